@@ -412,7 +412,8 @@ int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kin
         }
     } else {
         if constexpr (EPI == kEpiQkv || EPI == kEpiHead || EPI == kEpiPartial) return CLASP_E_UNSUPPORTED;
-        else launch_timed(timer, gemm_f32_kernel<EPI>, dim3(tiles), dim3(256), 0, st, g);
+        else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(tiles), dim3(512), 0, st, g);
+        else launch_timed(timer, gemm_f32_kernel<EPI, 2>, dim3(tiles), dim3(512), 0, st, g);
     }
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;

@@ -934,79 +934,153 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
     }
 }
 
-// fp32 path (small models / exactness checks): row-major fp32 weights, plain FMA. One workgroup (4 wavefronts) per
-// tile of 16 output features, each wavefront takes 4 of them and splits K across its lanes.
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g) {
-    constexpr int NACC = (EPI == kEpiSwiglu) ? 2 : 1;
-    __shared__ float rstd_s[kMaxRows];
-    __shared__ float tmp_s[256];
-    __shared__ float vals[NACC][16][kMaxRows];
+// fp32 path (small models / exactness checks): row-major fp32 weights on the fp32 matrix instruction. What bounds it is
+// latency: the fp32 models are small, a projection of the tiny one reads 0.25-1 MB, so everything a wavefront needs is
+// requested at once and the chain behind it is kept short. One workgroup per tile of 16 output features, eight
+// wavefronts that split K; a lane loads 16 bytes of W[feature lane%16] and of A[row lane%16] per 16 k (its four k are
+// step*16 + (lane/16)*4 + 0..3 on both sides, so element m of the two loads is one v_mfma_f32_16x16x4_f32, whose order of
+// k inside a step is free), and the four elements go into four accumulators, so that no sum is longer than K/128 + 10
+// additions. The slices are added in wavefront order through LDS; wavefront rg then runs the epilogue of row group rg on
+// a transposed tile (a lane owns four consecutive features of a row: 16-byte loads and stores).
+// Measured at d = 256, 5 rows: 47-85 us per launch with four features after one another per wavefront, a lane's FMAs for
+// 32 rows and 32 x 6 shuffles per feature; 4.1 us (projections onto d), 5.2 (q, k, v) and 6.6 (gate and up) now. Error
+// against 64 bits as before (2.8e-7 after eight layers).
+template <int EPI, int R>
+__global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
+    constexpr int KW = 8, NACC = (EPI == kEpiSwiglu) ? 2 : 1, P = 4;
+    constexpr bool kNeedsRstd = EPI != kEpiResid;
+    __shared__ f32x4 red[KW][NACC][R][64];
+    __shared__ float rstd_s[R][kMaxRows];
+    __shared__ float tmp_s[KW * 64];
     const int tile = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if constexpr (EPI != kEpiResid) compute_rstd(g, rstd_s, tmp_s);
-
+    const int c = lane & 15, q4 = lane >> 4;
+    const int KS = g.K >> 4;  // K % 16 == 0 (checked at create)
+    const int ks0 = (KS * wave) / KW, ks1 = (KS * (wave + 1)) / KW;
     int mi = 0, tl = tile;
     if constexpr (EPI == kEpiScale) {
         if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
         if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
     }
-    const float* A = reinterpret_cast<const float*>(g.A);
-    for (int c = 0; c < 4; ++c) {
-        const int cl = wave * 4 + c;
-        const float* wrow[NACC];
-        wrow[0] = reinterpret_cast<const float*>(g.W[mi]) + ((size_t)tl * 16 + cl) * g.K;
-        if constexpr (NACC == 2) wrow[1] = reinterpret_cast<const float*>(g.W[1]) + ((size_t)tl * 16 + cl) * g.K;
-        float acc[NACC][kMaxRows];
+    const f32x4* w[NACC];
 #pragma unroll
-        for (int a = 0; a < NACC; ++a)
+    for (int a = 0; a < NACC; ++a)
+        w[a] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.W[NACC == 2 ? a : mi]) +
+                                              ((size_t)tl * 16 + c) * g.K) + q4;
+    const f32x4* x[R];  // lanes of rows that do not exist read the last live row, their results are dropped
 #pragma unroll
-            for (int r = 0; r < kMaxRows; ++r) acc[a][r] = 0.f;
-        for (int k = lane; k < g.K; k += 64) {
-            float wv[NACC];
+    for (int rg = 0; rg < R; ++rg)
+        x[rg] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.A) + (size_t)min(rg * 16 + c, g.n_rows - 1) * g.K) + q4;
+
+    f32x4 acc[NACC][R][4];
 #pragma unroll
-            for (int a = 0; a < NACC; ++a) wv[a] = wrow[a][k];
+    for (int a = 0; a < NACC; ++a)
 #pragma unroll
-            for (int r = 0; r < kMaxRows; ++r) {
-                if (r < g.n_rows) {
-                    const float x = A[(size_t)r * g.K + k];
+        for (int rg = 0; rg < R; ++rg)
 #pragma unroll
-                    for (int a = 0; a < NACC; ++a) acc[a][r] = fmaf(wv[a], x, acc[a][r]);
-                }
+            for (int m = 0; m < 4; ++m) acc[a][rg][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    f32x4 wv[2][NACC][P], xv[2][R][P];
+    auto issue = [&](int b, int s) {
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            const size_t k = (size_t)min(s + u, ks1 - 1) * 4;
+#pragma unroll
+            for (int a = 0; a < NACC; ++a) wv[b][a][u] = w[a][k];
+#pragma unroll
+            for (int rg = 0; rg < R; ++rg) xv[b][rg][u] = x[rg][k];
+        }
+    };
+    auto compute = [&](int b, int s) {
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            if (s + u < ks1) {
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int rg = 0; rg < R; ++rg)
+#pragma unroll
+                        for (int a = 0; a < NACC; ++a)
+                            acc[a][rg][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[b][a][u][m], xv[b][rg][u][m], acc[a][rg][m], 0, 0, 0);
             }
         }
-#pragma unroll
-        for (int a = 0; a < NACC; ++a)
-#pragma unroll
-            for (int r = 0; r < kMaxRows; ++r) {
-                const float t = wave_sum(acc[a][r]);
-                if (lane == 0) vals[a][cl][r] = t;
-            }
+    };
+    int s = ks0;
+    if (s < ks1) issue(0, s);
+    float ssv[16];
+    if constexpr (kNeedsRstd) rstd_issue(g, ssv);
+    // inputs of the epilogue (wavefront rg: row rg*16 + c, features tile*16 + q4*4 .. +3)
+    const int row = wave * 16 + c, col0 = tile * 16 + q4 * 4;
+    f32x4 resid = f32x4{0.f, 0.f, 0.f, 0.f}, gain = f32x4{1.f, 1.f, 1.f, 1.f};
+    if constexpr (EPI == kEpiResid) {
+        if (wave < R) {
+            if (g.next_gain) gain = *reinterpret_cast<const f32x4*>(g.next_gain + col0);
+            if (row < g.n_rows) resid = *reinterpret_cast<const f32x4*>(g.resid + (size_t)row * g.ldr + col0);
+        }
     }
+    while (s < ks1) {
+        if (s + P < ks1) issue(1, s + P);
+        compute(0, s);
+        s += P;
+        if (s >= ks1) break;
+        if (s + P < ks1) issue(0, s + P);
+        compute(1, s);
+        s += P;
+    }
+#pragma unroll
+    for (int a = 0; a < NACC; ++a)
+#pragma unroll
+        for (int rg = 0; rg < R; ++rg)
+            red[wave][a][rg][lane] = (acc[a][rg][0] + acc[a][rg][1]) + (acc[a][rg][2] + acc[a][rg][3]);
+    if constexpr (kNeedsRstd) rstd_stash(g, ssv, tmp_s);
     __syncthreads();
-    // epilogue: one (row, column) pair per thread per pass; 16 consecutive lanes share a row
-    for (int idx = threadIdx.x; idx < 16 * kMaxRows; idx += 256) {
-        const int row = idx >> 4, cl = idx & 15, col = tile * 16 + cl;
-        float v = 0.f;
-        if constexpr (EPI == kEpiScale) {
-            if (row < g.n_rows) g.out[(size_t)row * g.ldo + col] = vals[0][cl][row] * rstd_s[row];
-        } else if constexpr (EPI == kEpiResid) {
-            if (row < g.n_rows) {
-                v = g.resid[(size_t)row * g.ldr + col] + vals[0][cl][row];
-                g.out[(size_t)row * g.ldo + col] = v;
-                if (g.capture) g.capture[(size_t)row * g.ldc + col] = v;
-                if (g.next_op)
-                    store_operand<kDtF32>(g.next_op, g.R, g.N, row, col, v * (g.next_gain ? g.next_gain[col] : 1.0f));
-            }
-            if (g.next_ss) {
-                const float sq = sum16(v * v);
-                if (cl == 0) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
-            }
+    if (wave >= R) return;
+    float rs = 1.0f;
+    if constexpr (kNeedsRstd) {
+        rstd_finish(g, tmp_s, rstd_s[wave]);
+        rs = rstd_s[wave][row];
+    }
+    f32x4 sum[NACC];
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) {
+        sum[a] = red[0][a][wave][lane];
+#pragma unroll
+        for (int k = 1; k < KW; ++k) sum[a] += red[k][a][wave][lane];
+    }
+    const bool live = row < g.n_rows;
+    auto store4 = [](float* base, int ld, int r, int col, const f32x4& v) {  // a caller's buffer may not be 16-byte aligned
+        float* p = base + (size_t)r * ld + col;
+        if ((reinterpret_cast<uintptr_t>(base) & 15) == 0 && (ld & 3) == 0) {
+            *reinterpret_cast<f32x4*>(p) = v;
         } else {
-            if (row < g.n_rows) {
-                const float gt = vals[0][cl][row] * rstd_s[row], up = vals[1][cl][row] * rstd_s[row];
-                v = gt / (1.0f + expf(-gt)) * up;
-                store_operand<kDtF32>(g.next_op, g.R, g.N, row, col, v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = v[e];
+        }
+    };
+    if constexpr (EPI == kEpiScale) {
+        if (live) store4(g.out, g.ldo, row, col0, sum[0] * rs);
+    } else if constexpr (EPI == kEpiResid) {
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (live) {
+            v = resid + sum[0];
+            *reinterpret_cast<f32x4*>(g.out + (size_t)row * g.ldo + col0) = v;
+            if (g.capture) store4(g.capture, g.ldc, row, col0, v);
+            if (g.next_op) store_operand4<kDtF32>(g.next_op, g.R, g.N, row, col0, v * gain);
+        }
+        if (g.next_ss) {
+            float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+            sq += __shfl_xor(sq, 16);
+            sq += __shfl_xor(sq, 32);
+            if (lane < 16) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
+        }
+    } else {
+        if (live) {
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float gt = sum[0][e] * rs, up = sum[NACC - 1][e] * rs;
+                v[e] = gt / (1.0f + expf(-gt)) * up;
             }
+            store_operand4<kDtF32>(g.next_op, g.R, g.N, row, col0, v);
         }
     }
 }
