@@ -483,8 +483,18 @@ int launch_attention(const clasp_ctx* ctx, int layer, int n, int R, int mode, in
     a.n_split = 1;
     TimerScope timer(ctx, CLASP_KERNEL_ATTENTION, st, true);
     if (c.dtype == CLASP_F32) {
-        const size_t lds = (size_t)(c.head_dim + pos0 + 32) * sizeof(float);
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(c.n_heads, n), dim3(256), lds, st, a);
+        const size_t lds = attn_f32_lds_floats(c.head_dim, pos0, mode ? n : 1) * sizeof(float);
+        auto kernel = c.head_dim % 8 == 0 ? attn_f32_kernel<true> : attn_f32_kernel<false>;
+        static bool opted_in[2] = {false, false};  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
+        bool& opted = opted_in[c.head_dim % 8 == 0];
+        if (!opted) {
+            constexpr size_t most = attn_f32_lds_floats(256, 8192, kMaxRows) * sizeof(float);  // check_config's limits
+            static_assert(most <= 160 * 1024, "LDS of a CU");
+            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
+                return CLASP_E_HIP;
+            opted = true;
+        }
+        hipLaunchKernelGGL(kernel, dim3(c.n_heads, n), dim3(256), lds, st, a);
         CLASP_LAUNCH_CHECK();
         return CLASP_OK;
     }

@@ -41,3 +41,54 @@ def verify_against_oracle(shape, row_counts, tol, max_seq=128):
 def test_fp32_projections_with_uneven_k_slices(d, heads, kv, hd, ffn):
     shape = si.ModelShape("edge-f32", 2, d, heads, kv, hd, ffn, 112, "f32")
     verify_against_oracle(shape, (1, 5, 16, 17, 32), 2e-5)
+
+
+def attention64(q, K, V, pos0):
+    """q [n][h][hd], K, V [pos0+n][kv][hd] in float64: row r sees positions 0..pos0+r."""
+    n, G = q.shape[0], q.shape[1] // K.shape[1]
+    t = torch.arange(pos0 + n)
+    out = torch.empty_like(q)
+    for r in range(n):
+        seen = t <= pos0 + r
+        for h in range(q.shape[1]):
+            p = torch.softmax((K[seen][:, h // G] @ q[r, h]) / q.shape[2] ** 0.5, 0)
+            out[r, h] = p @ V[seen][:, h // G]
+    return out
+
+
+# The fp32 attention takes keys 64 at a time and values in pieces of four positions of 64: no prefix, a piece with 1, 2 or 3
+# live positions, one below and above the 64 that are requested up front, several rounds; head_dim below, at and above the
+# 64 that are. One layer, so that the hidden state shows the attention: error of the softmax-weighted sum of up to 390
+# values and of its scores, each about sqrt(n) * 2^-24, then two projections.
+@pytest.mark.parametrize("heads,kv,hd", [(4, 4, 64), (4, 2, 16), (2, 1, 144)])
+@pytest.mark.parametrize("T", [0, 1, 62, 63, 64, 65, 387])
+def test_fp32_attention_at_the_edges_of_its_pieces(heads, kv, hd, T):
+    d = heads * hd
+    shape = si.ModelShape("edge-f32-attn", 1, d, heads, kv, hd, 64, 112, "f32")
+    eng, om = build(shape, max_seq=448)
+    K, V = si.gen_kv(shape, 9, 1, 448, "cpu")
+    bad = torch.full((448 - T, kv, hd), float("nan"))  # positions the call may not read
+    eng.clasp_kv_load(0, torch.cat([K[0, :T], bad]), torch.cat([V[0, :T], bad]))
+    n = 3
+    toks = [int(t) for t in si.gen_tokens(5, n, shape.vocab)]
+    out = eng.clasp_verify_forward(torch.tensor(toks, dtype=torch.int32, device="cuda"), T, want_hidden=True)
+    m = si.gen_model(shape, 3, "cpu")
+    w = {k: v.double() for k, v in m["layers"][0].items()}
+    x = m["embed"][toks].double()
+    rms = lambda v: v * torch.rsqrt((v * v).mean(-1, keepdim=True) + shape.rms_eps)  # noqa: E731
+    theta = shape.rope_base ** (-torch.arange(hd // 2, dtype=torch.float64) / (hd // 2))
+    ang = (T + torch.arange(n, dtype=torch.float64))[:, None, None] * theta
+
+    def rot(v):
+        a, b = v[..., :hd // 2], v[..., hd // 2:]
+        return torch.cat([a * ang.cos() - b * ang.sin(), b * ang.cos() + a * ang.sin()], -1)
+
+    q, k, v = rot((rms(x) @ w["wq"].T).view(n, heads, hd)), rot((rms(x) @ w["wk"].T).view(n, kv, hd)), (rms(x) @ w["wv"].T).view(n, kv, hd)
+    att = attention64(q, torch.cat([K[0, :T].double(), k]), torch.cat([V[0, :T].double(), v]), T)
+    a = x + att.reshape(n, d) @ w["wo"].T
+    y = a + (torch.nn.functional.silu(rms(a) @ w["w_gate"].T) * (rms(a) @ w["w_up"].T)) @ w["w_down"].T
+    assert_close(out["hidden"][1].cpu().numpy(), y.numpy(), 2e-5, f"T={T}")
+    rk, rv = eng.clasp_kv_read(0, T, n)
+    assert_close(rk.cpu().numpy().reshape(n, -1), k.reshape(n, -1).numpy(), 2e-5, "keys")
+    assert_close(rv.cpu().numpy().reshape(n, -1), v.reshape(n, -1).numpy(), 2e-5, "values")
+    eng.close()
