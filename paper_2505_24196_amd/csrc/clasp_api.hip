@@ -763,6 +763,20 @@ int dp_select_window(clasp_ctx* ctx, const float* states, size_t layer_stride, i
     return CLASP_OK;
 }
 
+// ---- stochastic decoding --------------------------------------------------------------------------------------------
+// The draws' scratch is the attention's partial results, which no call needs beyond its own layers.
+SampleArgs sample_args(const clasp_ctx* ctx, float temperature) {
+    const clasp_config& c = ctx->cfg;
+    // least size of that buffer: one KV head, one query head, head_dim 2
+    static_assert(kSampleScratchBytes <= (size_t)(2 * 1 + 4) * 16 * kMaxSplit * (2 + 2) * 4, "fits the smallest configuration");
+    SampleArgs a{};
+    a.V = c.vocab;
+    a.inv_t = 1.0f / temperature;
+    a.stats = reinterpret_cast<RowStat*>(ctx->attn_partial);
+    a.residual = reinterpret_cast<float*>(a.stats + (size_t)kSampleRows * kSampleChunks);
+    return a;
+}
+
 // ---- prompt processing with many rows per pass ---------------------------------------------------------------------
 #ifndef CLASP_PREFILL_BIG
 #define CLASP_PREFILL_BIG 1  // 256 x 256 tiles fed by direct global -> LDS loads where the grid is large enough
@@ -1325,8 +1339,12 @@ int clasp_sample_token(clasp_ctx* ctx, const float* logits, float temperature, c
                        void* stream) {
     if (!ctx || !logits || !u || !token_out || !(temperature > 0.f)) return CLASP_E_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(kSampleThreads), 0, st, logits, ctx->cfg.vocab, 1.0f / temperature, u,
-                       token_out);
+    SampleArgs a = sample_args(ctx, temperature);
+    a.p = logits; a.u_final = u; a.token_out = token_out;
+    const int chunks = sample_cut(a.V).chunks;
+    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 1), dim3(kSampleThreads), 0, st, a);
+    CLASP_LAUNCH_CHECK();
+    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, st, a);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
@@ -1349,8 +1367,15 @@ int clasp_spec_accept(clasp_ctx* ctx, const float* p_logits, const float* q_logi
     if (!(temperature > 0.f) || n_draft < 1 || n_draft > ctx->cfg.max_rows - 1 || ld < (size_t)ctx->cfg.vocab)
         return CLASP_E_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(spec_accept_kernel, dim3(1), dim3(kSampleThreads), 0, st, p_logits, q_logits, ld, tokens, n_draft,
-                       ctx->cfg.vocab, 1.0f / temperature, u_accept, u_final, n_accepted_out, next_token_out);
+    SampleArgs a = sample_args(ctx, temperature);
+    a.p = p_logits; a.q = q_logits; a.ld = ld; a.n = n_draft; a.tokens = tokens; a.u_accept = u_accept; a.u_final = u_final;
+    a.n_accepted_out = n_accepted_out; a.token_out = next_token_out;
+    const int chunks = sample_cut(a.V).chunks;
+    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 2 * n_draft + 1), dim3(kSampleThreads), 0, st, a);
+    CLASP_LAUNCH_CHECK();
+    hipLaunchKernelGGL(residual_sums_kernel, dim3(chunks), dim3(kDrawThreads), 0, st, a);
+    CLASP_LAUNCH_CHECK();
+    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, st, a);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }

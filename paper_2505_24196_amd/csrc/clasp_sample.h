@@ -1,155 +1,274 @@
 // Stochastic decoding (the paper's Temperature = 1 setting, Sec. 4; "still speculative sampling", Sec. 4.1): draws from
 // softmax(logits / T) by inverting the cumulative distribution with a uniform number the caller supplies, and the
-// speculative-sampling acceptance rule over one round of drafts. One 1024-thread workgroup per call: the work is a
-// few passes over [rows][vocab] fp32 logits (megabytes), nothing next to the forward passes around it.
-// Every sum runs in a fixed order (thread t owns the contiguous chunk of ceil(V/1024) entries starting at
-// t*ceil(V/1024)), so the same inputs give the same token on every run.
+// speculative-sampling acceptance rule over one round of drafts.
+// A row of 128k logits is half a megabyte: one workgroup pulls that at ~50 GB/s and needs it three times (maximum, sum,
+// draw), 10 us each. So the rows are cut into chunks, a workgroup each:
+//   chunk_stats_kernel     largest logit and sum of exp relative to it, per (row, chunk): the only pass over all rows
+//   residual_sums_kernel   (acceptance) every workgroup merges the rows' pieces, finds the first rejected draft for
+//                          itself (a few hundred words), and sums max(0, p - q) of its chunk of that row
+//   draw_kernel            one workgroup: running sums over the chunks' totals name the chunk that the draw falls into,
+//                          and only that chunk is read again
+// Measured at 128256 entries: one draw 202 us with one workgroup for everything, 12 us (4.6 + 7.3) now; acceptance of four
+// drafts 340 us (first draft rejected) to 1.4 ms, 17.5 us (3.8 + 4.9 + 6.8 and the boundaries) whichever is rejected.
+// Every sum runs in a fixed order, so the same inputs give the same token on every run.
 #pragma once
 #include "clasp_common.h"
 
 namespace clasp {
 
-constexpr int kSampleThreads = 1024;
-
-struct SampleShared {
-    float red[kSampleThreads / 64];
-    float part[kSampleThreads];   // per-thread chunk sums, then exclusive prefixes
-    float wave_tot[kSampleThreads / 64];
-    int pick;
-};
-
-__device__ __forceinline__ float block_max(float v, float* scratch) {
-    v = wave_max(v);
-    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[wave] = v;
-    __syncthreads();
-    float t = scratch[0];
-    for (int w = 1; w < nw; ++w) t = fmaxf(t, scratch[w]);
-    return t;
-}
+constexpr int kSampleThreads = 256;      // chunk_stats_kernel
+constexpr int kDrawThreads = 1024;       // the kernels that merge rows: a wavefront per row, sixteen rows at a time
+constexpr int kSampleChunks = 64;        // most chunks of a row: one lane each where they are merged
+constexpr int kSampleChunkMin = 1024;    // entries below which a row is not cut further
+constexpr int kSampleRows = 2 * kMaxRows - 1;  // p rows 0..n and q rows 0..n-1, n <= kMaxRows - 1
 
 struct RowStat {
     float m, s;  // max logit, sum over v of exp((logit_v - m) * inv_t)
 };
 
-__device__ __forceinline__ RowStat row_stat(const float* lg, int V, float inv_t, SampleShared& sh) {
-    const int C = (V + kSampleThreads - 1) / kSampleThreads;
-    const int lo = min(threadIdx.x * C, V), hi = min(lo + C, V);
-    float m = -INFINITY;
-    for (int v = lo; v < hi; ++v) m = fmaxf(m, lg[v]);
-    m = block_max(m, sh.red);
-    float s = 0.f;
-    for (int v = lo; v < hi; ++v) s += expf((lg[v] - m) * inv_t);
-    s = block_sum(s, sh.red);
-    return RowStat{m, s};
+// Chunks of a row of V entries and entries per chunk (the last chunk may be shorter, none is empty).
+struct SampleCut {
+    int chunks, size;
+};
+__host__ __device__ inline SampleCut sample_cut(int V) {
+    int size = (V + kSampleChunks - 1) / kSampleChunks;
+    size = size < kSampleChunkMin ? kSampleChunkMin : size;
+    return SampleCut{(V + size - 1) / size, size};
+}
+// Scratch: RowStat [kSampleRows][kSampleChunks], then the residual sums [kSampleChunks].
+constexpr size_t kSampleScratchBytes = (size_t)kSampleRows * kSampleChunks * sizeof(RowStat) + kSampleChunks * sizeof(float);
+
+struct SampleArgs {
+    const float* p;       // full model's rows (or the one row to draw from)
+    const float* q;       // draft model's rows, null for a plain draw
+    size_t ld;            // elements between rows
+    int n, V;             // drafts (0 for a plain draw), entries per row
+    float inv_t;
+    const int32_t* tokens;
+    const float *u_accept, *u_final;
+    int32_t *n_accepted_out, *token_out;
+    RowStat* stats;       // rows 0..n of p, then rows 0..n-1 of q
+    float* residual;
+};
+
+// A chunk's sum relative to the row's maximum m. A chunk without a finite maximum holds entries of weight 0 (sum 0) or NaN.
+__device__ __forceinline__ float rescaled(const RowStat& st, float m, float inv_t) {
+    return st.m == -INFINITY ? st.s : st.s * expf((st.m - m) * inv_t);
 }
 
-// Inverse-CDF draw from the non-negative weights w(0..V-1): the index v with c_{v-1} <= u * c_last < c_v, c = running
-// sums in index order. Returns the index to every thread (-1 when all weights are zero).
+// Merged (max, sum) of a row from its chunks' pieces, by one whole wavefront, the same in every lane.
+__device__ __forceinline__ RowStat merge_row(const RowStat* pieces, int chunks, float inv_t) {
+    const int lane = threadIdx.x & 63;
+    const RowStat st = lane < chunks ? pieces[lane] : RowStat{-INFINITY, 0.f};
+    const float m = wave_max(st.m);
+    return RowStat{m, wave_sum(rescaled(st, m, inv_t))};
+}
+
+// Grid (chunks, rows of p then rows of q).
+__global__ __launch_bounds__(kSampleThreads) void chunk_stats_kernel(SampleArgs a) {
+    __shared__ float red[kSampleThreads / 64], red2[kSampleThreads / 64];
+    const SampleCut cut = sample_cut(a.V);
+    const int row = blockIdx.y, lo = blockIdx.x * cut.size, hi = min(lo + cut.size, a.V);
+    const float* lg = row <= a.n ? a.p + (size_t)row * a.ld : a.q + (size_t)(row - a.n - 1) * a.ld;
+    // the first kKeep entries of a thread stay in registers (all of them up to 128k entries a row)
+    constexpr int kKeep = 8;
+    float keep[kKeep];
+    float m = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) {
+        const int v = lo + threadIdx.x + u * kSampleThreads;
+        keep[u] = v < hi ? lg[v] : -INFINITY;
+    }
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) m = fmaxf(m, keep[u]);
+    for (int v = lo + threadIdx.x + kKeep * kSampleThreads; v < hi; v += kSampleThreads) m = fmaxf(m, lg[v]);
+    m = wave_max(m);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) red[wave] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    auto weight = [&](float x) { return x == -INFINITY ? 0.f : expf((x - m) * a.inv_t); };  // also where all are -inf
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < kKeep; ++u) s += weight(keep[u]);
+    for (int v = lo + threadIdx.x + kKeep * kSampleThreads; v < hi; v += kSampleThreads) s += weight(lg[v]);
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red2[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) a.stats[(size_t)row * kSampleChunks + blockIdx.x] = RowStat{m, (red2[0] + red2[1]) + (red2[2] + red2[3])};
+}
+
+struct AcceptShared {
+    RowStat row[kSampleRows];
+    int reject[kMaxRows];
+};
+
+// The first rejected draft (n if none), by a whole workgroup; sh.row holds every row's (max, sum) afterwards. Draft i is
+// kept when u_accept[i] * q_i(x) < p_i(x).
+__device__ __forceinline__ int accept_prefix(const SampleArgs& a, int chunks, AcceptShared& sh) {
+    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, i = threadIdx.x;
+    float pl = 0.f, ql = 0.f, u = 0.f;  // this draft's logits and uniform number, requested beside the rows' pieces
+    if (i < a.n) {
+        const int x = min(max(a.tokens[i + 1], 0), a.V - 1);
+        pl = a.p[(size_t)i * a.ld + x];
+        ql = a.q[(size_t)i * a.ld + x];
+        u = a.u_accept[i];
+    }
+    for (int r = wave; r < 2 * a.n + 1; r += nw) {
+        const RowStat st = merge_row(a.stats + (size_t)r * kSampleChunks, chunks, a.inv_t);
+        if ((threadIdx.x & 63) == 0) sh.row[r] = st;
+    }
+    __syncthreads();
+    if (i < a.n) {
+        const RowStat ps = sh.row[i], qs = sh.row[a.n + 1 + i];
+        const float px = expf((pl - ps.m) * a.inv_t) / ps.s, qx = expf((ql - qs.m) * a.inv_t) / qs.s;
+        sh.reject[i] = !(u * qx < px);
+    }
+    __syncthreads();
+    int first = a.n;
+    for (int k = a.n - 1; k >= 0; --k)
+        if (sh.reject[k]) first = k;
+    return first;
+}
+
+struct ResidualWeight {  // max(0, p - q) of the first rejected row
+    const float *p, *q;
+    RowStat ps, qs;
+    float ip, iq, inv_t;
+    __device__ ResidualWeight(const SampleArgs& a, int row, const AcceptShared& sh)
+        : p(a.p + (size_t)row * a.ld), q(a.q + (size_t)row * a.ld), ps(sh.row[row]), qs(sh.row[a.n + 1 + row]),
+          ip(1.0f / ps.s), iq(1.0f / qs.s), inv_t(a.inv_t) {}
+    __device__ float operator()(int v) const {
+#pragma clang fp contract(off)  // equal logits have to leave exactly nothing, not the rounding of one of the products
+        const float pv = expf((p[v] - ps.m) * inv_t) * ip, qv = expf((q[v] - qs.m) * inv_t) * iq;
+        return fmaxf(pv - qv, 0.f);
+    }
+};
+
+// Grid (chunks). Leaves the chunk's residual mass at the first rejected draft.
+__global__ __launch_bounds__(kDrawThreads) void residual_sums_kernel(SampleArgs a) {
+    __shared__ AcceptShared sh;
+    __shared__ float red[kDrawThreads / 64];
+    const SampleCut cut = sample_cut(a.V);
+    const int lo = blockIdx.x * cut.size, hi = min(lo + cut.size, a.V);
+    const int first = accept_prefix(a, cut.chunks, sh);
+    if (first == a.n) return;
+    const ResidualWeight w(a, first, sh);
+    float s = 0.f;
+#pragma unroll 2
+    for (int v = lo + threadIdx.x; v < hi; v += kDrawThreads) s += w(v);
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.f;
+        for (int k = 0; k < kDrawThreads / 64; ++k) t += red[k];
+        a.residual[blockIdx.x] = t;
+    }
+}
+
+struct DrawShared {
+    float wave_tot[kDrawThreads / 64], wave_excl[kDrawThreads / 64];
+    int pick;
+    int last[kDrawThreads / 64];
+};
+
+// Inverse-CDF draw: the index v with c_{v-1} <= u * c_last < c_v, c = running sums of the weights w in index order.
+// `total` = this lane's chunk total (lane < chunks; the same in every wavefront). Returns the index to every thread, -1 when
+// the weights do not add up to a positive number.
 template <class WF>
-__device__ __forceinline__ int block_draw(WF w, int V, float u, SampleShared& sh) {
+__device__ __forceinline__ int draw_from_chunks(WF w, float total, const SampleCut& cut, int V, float u, DrawShared& sh) {
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int C = (V + kSampleThreads - 1) / kSampleThreads;
-    const int lo = min(t * C, V), hi = min(lo + C, V);
-    float local = 0.f;
-    for (int v = lo; v < hi; ++v) local += w(v);
-    __syncthreads();
-    sh.part[t] = local;
-    if (t == 0) sh.pick = -1;
-    __syncthreads();
-    if (lane == 0) {
-        float s = 0.f;
-        for (int k = 0; k < 64; ++k) s += sh.part[wave * 64 + k];
-        sh.wave_tot[wave] = s;
+    const float mine = lane < cut.chunks ? total : 0.f;
+    float incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float x = __shfl_up(incl, o);
+        if (lane >= o) incl += x;
     }
-    __syncthreads();
-    float excl = 0.f, total = 0.f;
-    for (int k = 0; k < kSampleThreads / 64; ++k) {
-        if (k < wave) excl += sh.wave_tot[k];
-        total += sh.wave_tot[k];
+    const float all = __shfl(incl, 63);
+    if (!(all > 0.f)) return -1;
+    const float target = u * all;
+    // the last chunk that has weight and starts at or below the target
+    const float before = __shfl_up(incl, 1), excl = lane ? before : 0.f;
+    const unsigned long long starts = __builtin_amdgcn_ballot_w64(mine > 0.f && excl <= target);
+    const int chunk = starts ? 63 - __builtin_clzll(starts) : __builtin_ctzll(__builtin_amdgcn_ballot_w64(mine > 0.f));
+    const float base = __shfl(excl, chunk);
+    const int first = chunk * cut.size, end = min(first + cut.size, V);
+    // the chunk again, in index order: a contiguous piece per thread
+    const int E = (end - first + kDrawThreads - 1) / kDrawThreads;
+    const int lo = min(first + t * E, end), hi = min(lo + E, end);
+    constexpr int kKeep = 2;  // weights that stay in registers: all of a thread's up to 128k entries a row
+    float keep[kKeep], local = 0.f;
+#pragma unroll
+    for (int e = 0; e < kKeep; ++e) keep[e] = lo + e < hi ? w(lo + e) : 0.f;
+#pragma unroll
+    for (int e = 0; e < kKeep; ++e) local += keep[e];
+    for (int v = lo + kKeep; v < hi; ++v) local += w(v);
+    float run = local;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float x = __shfl_up(run, o);
+        if (lane >= o) run += x;
     }
-    {
-        float s = 0.f;
-        for (int k = 0; k < lane; ++k) s += sh.part[wave * 64 + k];
-        excl += s;
-    }
+    __syncthreads();  // sh may still be read from an earlier draw
+    if (lane == 63) sh.wave_tot[wave] = run;
+    if (t == 0) sh.pick = 0x7fffffff;
     __syncthreads();
-    sh.part[t] = excl;  // non-decreasing in t
-    __syncthreads();
-    if (!(total > 0.f)) return -1;
-    const float target = u * total;
-    const bool owner = excl <= target && (t == kSampleThreads - 1 || target < sh.part[t + 1]);
-    if (owner) {  // exactly one thread; its chunk has positive weight unless it is the last thread
-        float run = excl;
-        int pick = -1, last = -1;
-        for (int v = lo; v < hi; ++v) {
-            const float wv = w(v);
-            run += wv;
-            if (wv > 0.f) last = v;
-            if (target < run) { pick = v; break; }
-        }
-        sh.pick = pick >= 0 ? pick : last;  // the running sum here may end an ulp short of the next thread's prefix
-    }
+    float wbase = base;
+    for (int k = 0; k < wave; ++k) wbase += sh.wave_tot[k];
+    const float prev = __shfl_up(run, 1);
+    float c = wbase + (lane ? prev : 0.f);
+    int last = -1;
+    int found = 0x7fffffff;
+    auto visit = [&](int v, float wv) {
+        c += wv;
+        if (wv > 0.f) last = v;
+        if (wv > 0.f && target < c) found = min(found, v);
+    };
+#pragma unroll
+    for (int e = 0; e < kKeep; ++e) visit(lo + e, keep[e]);
+    for (int v = lo + kKeep; v < hi; ++v) visit(v, w(v));
+    if (found != 0x7fffffff) atomicMin(&sh.pick, found);  // the lowest index whose running sum exceeds the target
+    // rounding may leave u * c_last at or beyond the last running sum: the chunk's last index of positive weight
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) last = max(last, __shfl_xor(last, o));
+    if (lane == 0) sh.last[wave] = last;
     __syncthreads();
     int pick = sh.pick;
-    if (pick < 0) {  // rounding left u * c_last at or beyond the last running sum: last index of positive weight
-        int last = -1;
-        for (int v = lo; v < hi; ++v)
-            if (w(v) > 0.f) last = v;
-        pick = (int)block_max((float)last, sh.red);  // indices < 2^24 are exact in fp32
+    if (pick == 0x7fffffff) {
+        pick = -1;
+        for (int k = 0; k < kDrawThreads / 64; ++k) pick = max(pick, sh.last[k]);
     }
     return pick;
 }
 
-// token_out[0] ~ softmax(logits / T) with the uniform number u[0].
-__global__ __launch_bounds__(kSampleThreads) void sample_kernel(const float* logits, int V, float inv_t, const float* u,
-                                                                int32_t* token_out) {
-    __shared__ SampleShared sh;
-    const RowStat st = row_stat(logits, V, inv_t, sh);
-    const int tok = block_draw([&](int v) { return expf((logits[v] - st.m) * inv_t); }, V, u[0], sh);
-    if (threadIdx.x == 0) token_out[0] = tok;
-}
-
-// One round of speculative sampling. tokens[0] is the round's pending token, tokens[1..n] the drafts; p row i / q row
-// i are the full / draft model's logits for the token after row i. Draft i is kept when
-// u_accept[i] * q_i(x) < p_i(x); the first rejected position a draws its replacement from max(0, p_a - q_a), and when
-// all n are kept the bonus token comes from p_n; both draws use u_final[0].
-__global__ __launch_bounds__(kSampleThreads) void spec_accept_kernel(const float* p_logits, const float* q_logits,
-                                                                     size_t ld, const int32_t* tokens, int n, int V,
-                                                                     float inv_t, const float* u_accept,
-                                                                     const float* u_final, int32_t* n_accepted_out,
-                                                                     int32_t* next_token_out) {
-    __shared__ SampleShared sh;
-    int a = n;
-    RowStat ps{}, qs{};
-    for (int i = 0; i < n; ++i) {  // every thread takes the same branches: all inputs of the test are block-uniform
-        const float* p = p_logits + (size_t)i * ld;
-        const float* q = q_logits + (size_t)i * ld;
-        ps = row_stat(p, V, inv_t, sh);
-        qs = row_stat(q, V, inv_t, sh);
-        const int x = min(max(tokens[i + 1], 0), V - 1);
-        const float px = expf((p[x] - ps.m) * inv_t) / ps.s, qx = expf((q[x] - qs.m) * inv_t) / qs.s;
-        if (!(u_accept[i] * qx < px)) {
-            a = i;
-            break;
-        }
-    }
-    const float* p = p_logits + (size_t)a * ld;
-    int tok = -1;
-    if (a < n) {
-        const float* q = q_logits + (size_t)a * ld;
-        const float ip = 1.0f / ps.s, iq = 1.0f / qs.s;
-        tok = block_draw(
-            [&](int v) { return fmaxf(expf((p[v] - ps.m) * inv_t) * ip - expf((q[v] - qs.m) * inv_t) * iq, 0.f); }, V,
-            u_final[0], sh);
+// One workgroup. Plain draw (q null): token ~ softmax(p / T). Acceptance: the replacement of the first rejected draft from
+// its residual, or from the full model's row where the residual is empty; the bonus token from row n when all are kept.
+__global__ __launch_bounds__(kDrawThreads) void draw_kernel(SampleArgs a) {
+    __shared__ AcceptShared ac;
+    __shared__ DrawShared sh;
+    const SampleCut cut = sample_cut(a.V);
+    const int lane = threadIdx.x & 63;
+    const float u = a.u_final[0];
+    int row = 0, tok = -1;
+    RowStat ps;
+    if (a.q) {
+        const float mass = lane < cut.chunks ? a.residual[lane] : 0.f;  // unwritten, and not used, when all drafts are kept
+        row = accept_prefix(a, cut.chunks, ac);
+        ps = ac.row[row];
+        if (row < a.n) tok = draw_from_chunks(ResidualWeight(a, row, ac), mass, cut, a.V, u, sh);
     } else {
-        ps = row_stat(p, V, inv_t, sh);
+        ps = merge_row(a.stats, cut.chunks, a.inv_t);
     }
-    if (tok < 0) tok = block_draw([&](int v) { return expf((p[v] - ps.m) * inv_t); }, V, u_final[0], sh);
-    if (threadIdx.x == 0) {
-        n_accepted_out[0] = a;
-        next_token_out[0] = tok;
+    if (tok < 0) {
+        const float* p = a.p + (size_t)row * a.ld;
+        const RowStat st = lane < cut.chunks ? a.stats[(size_t)row * kSampleChunks + lane] : RowStat{-INFINITY, 0.f};
+        tok = draw_from_chunks([&](int v) { return expf((p[v] - ps.m) * a.inv_t); }, rescaled(st, ps.m, a.inv_t), cut, a.V, u, sh);
+    }
+    if (threadIdx.x == 0) {  // outputs last: every input of the call has been read by now
+        if (a.q) a.n_accepted_out[0] = row;
+        a.token_out[0] = tok;
     }
 }
 

@@ -92,3 +92,65 @@ def test_fp32_attention_at_the_edges_of_its_pieces(heads, kv, hd, T):
     assert_close(rk.cpu().numpy().reshape(n, -1), k.reshape(n, -1).numpy(), 2e-5, "keys")
     assert_close(rv.cpu().numpy().reshape(n, -1), v.reshape(n, -1).numpy(), 2e-5, "values")
     eng.close()
+
+
+# Draws and acceptance over rows cut into chunks: one chunk, a last chunk of 16 entries, 64 full chunks, chunks larger than
+# the entries kept in registers. The mass sits on at most eight tokens, several of them at chunk edges. A running sum of the
+# others' weights (e^-39 each) is exact to 1e-7, of the eight and of their fp32 exponentials to 16 * 2^-23 + 8 * 2^-24 = 2.4e-6:
+# draws whose uniform number is further than 1e-4 from every float64 running sum have to agree.
+@pytest.mark.parametrize("V", [16, 1024, 1040, 2064, 65536, 128256, 262160])
+def test_draws_over_chunk_edges(V):
+    import paper_2505_24196_amd as clasp
+    shape = si.ModelShape("edge-vocab", 1, 32, 2, 1, 16, 32, V, "f32")
+    eng = clasp.Engine(shape, max_seq=32, max_rows=32).load(si.gen_model(shape, 3, "cuda"))
+    size = max(1024, (V + 63) // 64)
+    hot = sorted({0, 1, size - 1, size, 2 * size, V // 2, V - 2, V - 1} & set(range(V)))
+    base = torch.full((V,), -40.0)
+    base[hot] = torch.linspace(-1.0, 1.0, len(hot))
+    dev = lambda t: t.to("cuda")  # noqa: E731
+    tok, acc = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    variants = {"plain": base, "inf": torch.where(base < -30, torch.tensor(-float("inf")), base),
+                "lowest": torch.where(base < -30, torch.tensor(torch.finfo(torch.float32).min), base)}
+    checked = 0
+    for lg in variants.values():
+        c = torch.softmax(lg.double() / 0.8, 0).cumsum(0)
+        d_lg = dev(lg)
+        for u in [0.0, 1 - 2.0 ** -24] + [(i + 0.5) / 23 for i in range(23)]:
+            eng.clasp_sample_token(d_lg, 0.8, torch.tensor([u], device="cuda"), tok)
+            assert lg[int(tok)] > -30
+            if (c - u).abs().min() > 1e-4:
+                assert int(tok) == int((c > u).nonzero()[0]), (u, V)
+                checked += 1
+    assert checked > 40
+    for bad in (torch.full((V,), -float("inf")), torch.full((V,), float("nan"))):  # no distribution: -1
+        eng.clasp_sample_token(dev(bad), 1.0, torch.tensor([0.5], device="cuda"), tok)
+        assert int(tok) == -1
+    one_nan = base.clone()
+    one_nan[V - 1] = float("nan")
+    eng.clasp_sample_token(dev(one_nan), 1.0, torch.tensor([0.5], device="cuda"), tok)
+    assert int(tok) == -1
+    # acceptance: n drafts, the first rejected one at every place (its draft has probability ~0 under the full model)
+    for n in (1, 5, 31):
+        for a in sorted({0, n // 2, n - 1, n}):
+            p, q = base.repeat(n + 1, 1), base.repeat(n, 1)
+            drafts = [hot[i % len(hot)] for i in range(n)]
+            if a < n:
+                q[a, hot[0]] += 2.0
+                p[a, drafts[a]] = -40.0
+            u = 0.37
+            eng.clasp_spec_accept(dev(p), dev(q), torch.tensor([0] + drafts, dtype=torch.int32, device="cuda"), n, 1.0,
+                                  torch.full((n,), 0.5, device="cuda"), torch.tensor([u], device="cuda"), acc, tok)
+            w = torch.softmax(p[a].double(), 0)
+            if a < n:
+                w = (w - torch.softmax(q[a].double(), 0)).clamp_min(0)
+            c = w.cumsum(0) / w.sum()
+            assert int(acc) == a, (V, n, a)
+            if (c - u).abs().min() > 1e-4:
+                assert int(tok) == int((c > u).nonzero()[0]), (V, n, a)
+    # identical rows and a rejection by u: the residual is empty and the full model's row is drawn from
+    p = base.repeat(2, 1)
+    eng.clasp_spec_accept(dev(p), dev(base[None]), torch.tensor([0, hot[0]], dtype=torch.int32, device="cuda"), 1, 1.0,
+                          torch.full((1,), 1.0, device="cuda"), torch.tensor([0.37], device="cuda"), acc, tok)
+    c = torch.softmax(base.double(), 0).cumsum(0)
+    assert int(acc) == 0 and int(tok) == int((c > 0.37).nonzero()[0])
+    eng.close()
