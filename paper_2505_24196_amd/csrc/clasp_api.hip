@@ -777,18 +777,20 @@ SampleArgs sample_args(const clasp_ctx* ctx, float temperature) {
     return a;
 }
 
+int launch_draw(const SampleArgs& a, hipStream_t st) {
+    const int chunks = sample_cut(a.V).chunks;
+    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 2 * a.n + 1), dim3(kSampleThreads), 0, st, a);
+    CLASP_LAUNCH_CHECK();
+    if (a.q) {
+        hipLaunchKernelGGL(residual_sums_kernel, dim3(chunks), dim3(kDrawThreads), 0, st, a);
+        CLASP_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, st, a);
+    CLASP_LAUNCH_CHECK();
+    return CLASP_OK;
+}
+
 // ---- prompt processing with many rows per pass ---------------------------------------------------------------------
-#ifndef CLASP_PREFILL_BIG
-#define CLASP_PREFILL_BIG 1  // 256 x 256 tiles fed by direct global -> LDS loads where the grid is large enough
-#endif
-// The big tiles are taken when they give at least this fraction of the CUs a workgroup: half (measured at the 8B
-// shape: 512 tokens 18.9 -> 15.9 ms, 3072 tokens 63.3 -> 50.3 ms against "every CU"; a third costs short passes).
-#ifndef CLASP_PREFILL_BIG_FILL_NUM
-#define CLASP_PREFILL_BIG_FILL_NUM 1
-#endif
-#ifndef CLASP_PREFILL_BIG_FILL_DEN
-#define CLASP_PREFILL_BIG_FILL_DEN 2
-#endif
 constexpr int kPrefillMaxChunk = 8192;
 // Passes of at least this many rows (640: measured break-even at the 8B shape is between 512 and 640) run their GEMMs on fp16 MFMAs: one fp16 plane per activation instead of the bf16
 // hi / lo pair (half the matrix-core work) against an fp16 copy of the layer's weights made at the start of the layer
@@ -804,7 +806,7 @@ struct PrefillWs {
 };
 
 bool prefill_uses_f16(int rows) { return CLASP_PREFILL_F16_ROWS > 0 && rows >= CLASP_PREFILL_F16_ROWS; }
-constexpr int kPrefillSplitRows = 1024, kPrefillMaxSplit = 4;  // K-split of short passes: rows it applies to, slices
+constexpr int kPrefillSplitRows = 1024, kPrefillMaxSplit = 4;  // K-split: most slices, room for that many of this many rows
 
 size_t carve_prefill(const clasp_config& c, int chunk, char* base, PrefillWs* ws) {
     Carver w{base};
@@ -828,88 +830,140 @@ size_t carve_prefill(const clasp_config& c, int chunk, char* base, PrefillWs* ws
     return w.off;
 }
 
-// Which GEMM kernel a projection of the prompt pass takes (measured at the 8B shape):
-//  * o_proj, gate|up, down: 256 x 256 tiles fed by direct global -> LDS loads when they give at least half of the CUs a
-//    workgroup (gate|up from 257 rows on, the projections onto d_model from 1793 rows on), else 128 x 128 tiles, two
-//    workgroups per CU;
-//  * q/k/v: in fp16 passes 256 x 192 tiles of the same kernel (two full rounds of CUs at 4096 rows) under the same
-//    condition; in bf16 passes (hi + lo planes: its epilogue does not fit the big tile's register budget) 128 x 128
-//    tiles with three lighter workgroups per CU;
-//  * any of them: 64 x 128 tiles when even the 128 x 128 grid has fewer workgroups than CUs.
-//  F16: the pass runs on fp16 operands (p.g.A is an fp16 plane, p.g.W an fp16 copy of the weights).
+// ---- which workgroup tile a projection of the prompt pass takes -------------------------------------------------------
+// A tile of prefill_ring_kernel with what a workgroup of it costs, in microseconds per 128 k-steps (measured at the 8B
+// shape's projections): `alone` when the launch gives a CU one workgroup, `shared` per workgroup when it gives a CU several
+// in a row (or two at a time: the four-wavefront tiles).
+template <int WM_, int WN_, int RM_, int RN_, int STAGES_, int ALONE, int SHARED>
+struct RingTile {
+    static constexpr int WM = WM_, WN = WN_, RM = RM_, RN = RN_, STAGES = STAGES_;
+    static constexpr int rows = WM * RM, cols = WN * RN;  // in 16 x 16 tiles
+    static constexpr float alone = ALONE, shared = SHARED;
+};
+template <class... T>
+struct RingTiles {};
+
+// bf16 passes (65..639 rows, hi + lo planes)
+using T32x128 = RingTile<2, 2, 1, 4, 5, 33, 26>;
+using T64x128 = RingTile<2, 2, 2, 4, 5, 43, 37>;
+using T96x128 = RingTile<2, 2, 3, 4, 4, 53, 46>;
+using T64x256 = RingTile<2, 4, 2, 4, 5, 66, 62>;
+using T96x256 = RingTile<2, 4, 3, 4, 5, 90, 88>;
+using T128x256 = RingTile<2, 4, 4, 4, 5, 112, 107>;
+using T160x256 = RingTile<2, 4, 5, 4, 4, 130, 129>;
+// fp16 passes (640 rows or more, one plane)
+using H128x128 = RingTile<2, 2, 4, 4, 5, 52, 38>;
+using H160x128 = RingTile<2, 2, 5, 4, 4, 58, 43>;
+using H192x128 = RingTile<2, 2, 6, 4, 4, 64, 48>;
+using H128x192 = RingTile<2, 2, 4, 6, 4, 65, 53>;
+using H128x256 = RingTile<2, 2, 4, 8, 3, 82, 64>;
+using H256x128 = RingTile<4, 2, 4, 4, 5, 72, 68>;
+using H256x192 = RingTile<4, 2, 4, 6, 4, 98, 101>;
+using H192x256 = RingTile<2, 4, 6, 4, 4, 96, 96>;
+using H256x256 = RingTile<4, 2, 4, 8, 4, 118, 120>;
+
 template <int EPI, bool F16>
-int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStream_t st, float* parts = nullptr) {
-    const int tiles = p.g.N / 16;
-    if constexpr (EPI != kEpiQkv || F16) {
-        // q/k/v (fp16 passes only: with the bf16 planes its epilogue does not fit the registers): 192 columns per workgroup
-        constexpr int RN = EPI == kEpiQkv ? 6 : 8;
-        const int nrb = (p.g.R * 16 + kPrefillBigRows - 1) / kPrefillBigRows, total = nrb * ((tiles + 2 * RN - 1) / (2 * RN));
-        // (the fp16 variant of the big tile walks the contraction in pairs of k-steps)
-        if (CLASP_PREFILL_BIG && total * CLASP_PREFILL_BIG_FILL_DEN >= ctx->n_cu * CLASP_PREFILL_BIG_FILL_NUM && (!F16 || (p.g.K / 32) % 2 == 0)) {
-            static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-            auto kernel = prefill_gemm256_kernel<EPI, F16, RN>;
-            constexpr size_t big_lds = prefill_big_lds<F16, RN>();
-            if (!opted_in) {
-                if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)big_lds) !=
-                    hipSuccess)
-                    return CLASP_E_HIP;
-                opted_in = true;
-            }
-            hipLaunchKernelGGL(kernel, dim3((total + 7) / 8 * 8), dim3(512), big_lds, st, p);
+constexpr auto ring_tiles() {
+    if constexpr (F16) {
+        if constexpr (EPI == kEpiQkv) return RingTiles<H128x128, H192x128, H128x192, H256x128, H256x192>{};
+        else if constexpr (EPI == kEpiSwiglu) return RingTiles<H160x128, H192x128, H128x192, H128x256, H256x256>{};
+        else if constexpr (EPI == kEpiPartial) return RingTiles<H160x128, H256x128, H192x256, H256x256>{};
+        else return RingTiles<H256x128, H192x256, H256x256>{};
+    } else {
+        if constexpr (EPI == kEpiQkv) return RingTiles<T32x128, T64x128, T96x128, T64x256>{};
+        else if constexpr (EPI == kEpiSwiglu) return RingTiles<T64x128, T64x256, T96x256, T128x256, T160x256>{};
+        else return RingTiles<T64x128, T64x256, T96x256, T128x256, T160x256>{};
+    }
+}
+
+// The cheapest tile (index into the list) and K-split of a launch, by whole rounds of CUs: a workgroup costs its k-steps
+// plus about 24 more for its first loads and its epilogue.
+struct RingPick {
+    int tile = 0, split = 1;
+    float us = INFINITY;
+};
+template <class T>
+void consider(RingPick& best, int index, int split, int R, int n_tiles, int ks, int n_cu, float extra_us) {
+    const long long wgs = (long long)((R + T::rows - 1) / T::rows) * ((n_tiles + T::cols - 1) / T::cols) * split;
+    const float each = wgs <= n_cu ? T::alone : T::shared * (float)((wgs + n_cu - 1) / n_cu);
+    const float us = each * ((float)ks / split + 24.f) / 152.f + extra_us;
+    if (us < best.us) best = RingPick{index, split, us};
+}
+template <class... T>
+RingPick pick_ring(RingTiles<T...>, int split, int R, int n_tiles, int ks, int n_cu, float extra_us) {
+    RingPick best;
+    int index = 0;
+    (consider<T>(best, index++, split, R, n_tiles, ks, n_cu, extra_us), ...);
+    return best;
+}
+
+template <int EPI, bool F16, class T>
+int launch_ring(const PrefillGemmArgs& p, int split, hipStream_t st) {
+    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
+    auto kernel = prefill_ring_kernel<EPI, F16, T::WM, T::WN, T::RM, T::RN, T::STAGES, 2>;
+    constexpr size_t lds = (size_t)T::STAGES * prefill_ring_frags<F16, T::WM, T::WN, T::RM, T::RN>() * 1024;
+    static_assert(lds <= 160 * 1024, "LDS of a CU");
+    if (!opted_in) {
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+            return CLASP_E_HIP;
+        opted_in = true;
+    }
+    const int total = ((p.g.R + T::rows - 1) / T::rows) * ((p.g.N / 16 + T::cols - 1) / T::cols);
+    hipLaunchKernelGGL(kernel, dim3((total + 7) / 8 * 8, split), dim3(T::WM * T::WN * 64), lds, st, p);
+    CLASP_LAUNCH_CHECK();
+    return CLASP_OK;
+}
+template <int EPI, bool F16, class... T>
+int launch_picked(RingTiles<T...>, const RingPick& pick, const PrefillGemmArgs& p, hipStream_t st) {
+    int index = 0, rc = CLASP_E_UNSUPPORTED;
+    ((index++ == pick.tile ? (void)(rc = launch_ring<EPI, F16, T>(p, pick.split, st)) : (void)0), ...);
+    return rc;
+}
+
+// One projection. F16: the pass runs on fp16 operands (p.g.A is an fp16 plane, p.g.W an fp16 copy of the weights). The
+// residual projections (N = d_model, too few columns for the CUs below some 4000 rows) may split the contraction over
+// workgroups: the slices go to `parts` (room for part_rows rows) and prefill_reduce_kernel finishes them; without a split
+// the epilogue runs in the GEMM and prefill_rstd_kernel adds up its sums of squares. bf16 passes are short enough to
+// always take the first way, fp16 passes take the cheaper one.
+template <int EPI, bool F16>
+int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStream_t st, float* parts = nullptr,
+                        size_t part_rows = 0) {
+    const int n_tiles = p.g.N / 16, ks = p.g.K / 32, R = p.g.R, n = p.g.n_rows;
+    if constexpr (EPI == kEpiResid) {
+        RingPick best, direct;
+        for (int split = 1; split <= kPrefillMaxSplit && split <= ks && (size_t)split * n <= part_rows; ++split) {
+            // reduction: the slices, the residual and what comes out, at 4 TB/s, and a launch
+            const float reduce_us = 4.f + (float)n * p.g.N * 4.f * (split + 3) / 4e6f;
+            const RingPick t = pick_ring(ring_tiles<kEpiPartial, F16>(), split, R, n_tiles, ks, ctx->n_cu, reduce_us);
+            if (t.us < best.us) best = t;
+        }
+        if constexpr (F16) direct = pick_ring(ring_tiles<kEpiResid, F16>(), 1, R, n_tiles, ks, ctx->n_cu, 4.f);
+        int rc;
+        if (best.us < direct.us) {
+            PrefillGemmArgs q = p;
+            q.slab = (size_t)n * p.g.ldo;
+            q.g.out = parts;
+            if ((rc = launch_picked<kEpiPartial, F16>(ring_tiles<kEpiPartial, F16>(), best, q, st))) return rc;
+            q.g.out = p.g.out;
+            static_assert(kPrefillMaxSplit == 4, "the cases below");
+            auto reduce = best.split == 1 ? prefill_reduce_kernel<1, F16> : best.split == 2 ? prefill_reduce_kernel<2, F16>
+                        : best.split == 3 ? prefill_reduce_kernel<3, F16> : prefill_reduce_kernel<4, F16>;
+            using B = RowBlock<F16>;
+            hipLaunchKernelGGL(reduce, dim3((n + B::kRows - 1) / B::kRows), dim3(B::kThreads), 0, st, q, parts);
             CLASP_LAUNCH_CHECK();
             return CLASP_OK;
         }
-    }
-    auto launch = [&](auto kernel, size_t lds, int rows, bool& opted) -> int {
-        if (!opted) {  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                return CLASP_E_HIP;
-            opted = true;
+        if constexpr (F16) {
+            if ((rc = launch_picked<kEpiResid, F16>(ring_tiles<kEpiResid, F16>(), direct, p, st))) return rc;
+            hipLaunchKernelGGL(prefill_rstd_kernel, dim3((n + 63) / 64), dim3(64, 16), 0, st, p.g.next_ss, n_tiles, p.ld_ss, n,
+                               p.inv_dim, p.eps, p.next_rstd);
+            CLASP_LAUNCH_CHECK();
+            return CLASP_OK;
         }
-        const int total = ((p.g.R * 16 + rows - 1) / rows) * ((tiles + 7) / 8);
-        hipLaunchKernelGGL(kernel, dim3((total + 7) / 8 * 8), dim3(256), lds, st, p);
-        CLASP_LAUNCH_CHECK();
-        return CLASP_OK;
-    };
-    static bool opted_in[2] = {false, false};
-    // 64-row tiles when 128-row tiles would not give every CU a workgroup (prompts of a few hundred tokens)
-    const int total128 = ((p.g.R * 16 + kPrefillRows - 1) / kPrefillRows) * ((tiles + 7) / 8);
-    if (total128 < ctx->n_cu || (EPI == kEpiResid && p.g.n_rows <= kPrefillSplitRows && total128 < 2 * ctx->n_cu)) {
-        if constexpr (EPI == kEpiResid) {
-            // ... and when even those leave most of the three workgroup slots per CU empty, the contraction is split over
-            // gridDim.y workgroups as well (o_proj and down at 512 rows: 256 workgroups of 128 / 448 k-steps otherwise);
-            // the slices are summed in order by a second kernel that also runs the epilogue
-            const int total = ((p.g.R * 16 + 63) / 64) * ((tiles + 7) / 8);
-            int split = (3 * ctx->n_cu) / (total > 0 ? total : 1);
-            split = split > kPrefillMaxSplit ? kPrefillMaxSplit : split;
-            while (split >= 2 && p.g.K / 32 < 16 * split) --split;  // at least 16 k-steps per slice
-            if (parts && split >= 2 && p.g.n_rows <= kPrefillSplitRows) {
-                static bool split_opted_in = false;
-                auto kernel = prefill_gemm_kernel<kEpiPartial, 2, 4, 2, 3, F16>;
-                constexpr size_t lds = prefill_gemm_lds_bytes<2, 4, 2, F16>();
-                if (!split_opted_in) {
-                    if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                        return CLASP_E_HIP;
-                    split_opted_in = true;
-                }
-                PrefillGemmArgs q = p;
-                q.k_split = split;
-                q.slab = (size_t)p.g.n_rows * p.g.ldo;
-                q.g.out = parts;
-                hipLaunchKernelGGL(kernel, dim3((total + 7) / 8 * 8, split), dim3(256), lds, st, q);
-                CLASP_LAUNCH_CHECK();
-                q.g.out = p.g.out;
-                hipLaunchKernelGGL(prefill_reduce_kernel, dim3(p.g.n_rows, (p.g.N + 255) / 256), dim3(256), 0, st, q, parts);
-                CLASP_LAUNCH_CHECK();
-                return CLASP_OK;
-            }
-        }
-        constexpr size_t lds64 = prefill_gemm_lds_bytes<2, 4, 2, F16>();
-        return launch(prefill_gemm_kernel<EPI, 2, 4, 2, 3, F16>, lds64, 64, opted_in[0]);
+        return CLASP_E_UNSUPPORTED;  // not reached: the slices of a bf16 pass always fit
+    } else {
+        return launch_picked<EPI, F16>(ring_tiles<EPI, F16>(), pick_ring(ring_tiles<EPI, F16>(), 1, R, n_tiles, ks, ctx->n_cu, 0.f), p, st);
     }
-    constexpr int D = EPI == kEpiQkv ? 1 : 2, WPS = EPI == kEpiQkv ? 3 : 2;
-    constexpr size_t lds128 = prefill_gemm_lds_bytes<4, 4, D, F16>();
-    return launch(prefill_gemm_kernel<EPI, 4, 4, D, WPS, F16>, lds128, kPrefillRows, opted_in[1]);
 }
 
 // Attention of a chunk: long prefixes share the key / value blocks of a workgroup through LDS, short ones (a few blocks
@@ -957,13 +1011,19 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
     const int d = c.d_model, F = c.d_ffn, L = c.n_layers, R = (n + 15) / 16;
     const bool f16 = ws.w16 && prefill_uses_f16(n);
     int rc;
-    hipLaunchKernelGGL(prefill_embed_kernel, dim3(n, (d + 255) / 256), dim3(256), 0, st, tokens,
-                       static_cast<const bf16*>(ctx->embed), c.vocab, d, ws.h, ws.op_h, R, ctx->attn_norm[0], ws.ss_h, ld,
-                       (int)f16);
-    CLASP_LAUNCH_CHECK();
+    {
+        auto kernel = f16 ? prefill_embed_kernel<true> : prefill_embed_kernel<false>;
+        const int rows = f16 ? RowBlock<true>::kRows : RowBlock<false>::kRows;
+        const int threads = f16 ? RowBlock<true>::kThreads : RowBlock<false>::kThreads;
+        hipLaunchKernelGGL(kernel, dim3((n + rows - 1) / rows), dim3(threads), 0, st, tokens, static_cast<const bf16*>(ctx->embed),
+                           c.vocab, d, n, ws.h, ws.op_h, R, ctx->attn_norm[0], ws.rstd_h, c.rms_eps);
+        CLASP_LAUNCH_CHECK();
+    }
+    const size_t part_rows = (size_t)kPrefillMaxSplit * std::min(ld, kPrefillSplitRows);
     auto gemm = [&](auto epi, const PrefillGemmArgs& p, float* parts) -> int {
         constexpr int EPI = decltype(epi)::value;
-        return f16 ? launch_prefill_gemm<EPI, true>(ctx, p, st, parts) : launch_prefill_gemm<EPI, false>(ctx, p, st, parts);
+        return f16 ? launch_prefill_gemm<EPI, true>(ctx, p, st, parts, part_rows)
+                   : launch_prefill_gemm<EPI, false>(ctx, p, st, parts, part_rows);
     };
     for (int l = 0; l < L; ++l) {
         // this layer's matrices, as packed or as the fp16 copy made here (the last layer only runs q/k/v)
@@ -984,9 +1044,6 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
             hipLaunchKernelGGL(prefill_convert_f16_kernel, dim3(ctx->n_cu * 8), dim3(256), 0, st, cv);
             CLASP_LAUNCH_CHECK();
         }
-        hipLaunchKernelGGL(prefill_rstd_kernel, dim3((n + 63) / 64), dim3(64, 16), 0, st, ws.ss_h, d / 16, ld, n, 1.0f / d,
-                           c.rms_eps, ws.rstd_h);
-        CLASP_LAUNCH_CHECK();
         {
             PrefillGemmArgs p{};
             GemmArgs& g = p.g;
@@ -1021,11 +1078,9 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
             g.A = ws.op_attn; g.n_rows = n; g.N = d; g.K = ctx->q_dim; g.R = R;
             g.out = ws.a_buf; g.ldo = d; g.resid = ws.h; g.ldr = d;
             g.next_op = ws.op_a; g.next_gain = ctx->mlp_norm[l]; g.next_ss = ws.ss_a; p.ld_ss = ld; p.op_f16 = f16;
+            p.next_rstd = ws.rstd_a; p.inv_dim = 1.0f / d; p.eps = c.rms_eps;
             if ((rc = gemm(std::integral_constant<int, kEpiResid>{}, p, ws.parts))) return rc;
         }
-        hipLaunchKernelGGL(prefill_rstd_kernel, dim3((n + 63) / 64), dim3(64, 16), 0, st, ws.ss_a, d / 16, ld, n, 1.0f / d,
-                           c.rms_eps, ws.rstd_a);
-        CLASP_LAUNCH_CHECK();
         {
             PrefillGemmArgs p{};
             GemmArgs& g = p.g;
@@ -1042,6 +1097,7 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
             g.A = ws.op_act; g.n_rows = n; g.N = d; g.K = F; g.R = R;
             g.out = ws.h; g.ldo = d; g.resid = ws.a_buf; g.ldr = d;
             g.next_op = ws.op_h; g.next_gain = ctx->attn_norm[l + 1]; g.next_ss = ws.ss_h; p.ld_ss = ld; p.op_f16 = f16;
+            p.next_rstd = ws.rstd_h; p.inv_dim = 1.0f / d; p.eps = c.rms_eps;
             if ((rc = gemm(std::integral_constant<int, kEpiResid>{}, p, ws.parts))) return rc;
         }
     }
@@ -1341,12 +1397,7 @@ int clasp_sample_token(clasp_ctx* ctx, const float* logits, float temperature, c
     hipStream_t st = static_cast<hipStream_t>(stream);
     SampleArgs a = sample_args(ctx, temperature);
     a.p = logits; a.u_final = u; a.token_out = token_out;
-    const int chunks = sample_cut(a.V).chunks;
-    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 1), dim3(kSampleThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    return CLASP_OK;
+    return launch_draw(a, st);
 }
 
 int clasp_draft_sample(clasp_ctx* ctx, const uint8_t* mask, const int32_t* token, int pos, float temperature,
@@ -1370,14 +1421,7 @@ int clasp_spec_accept(clasp_ctx* ctx, const float* p_logits, const float* q_logi
     SampleArgs a = sample_args(ctx, temperature);
     a.p = p_logits; a.q = q_logits; a.ld = ld; a.n = n_draft; a.tokens = tokens; a.u_accept = u_accept; a.u_final = u_final;
     a.n_accepted_out = n_accepted_out; a.token_out = next_token_out;
-    const int chunks = sample_cut(a.V).chunks;
-    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 2 * n_draft + 1), dim3(kSampleThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(residual_sums_kernel, dim3(chunks), dim3(kDrawThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    hipLaunchKernelGGL(draw_kernel, dim3(1), dim3(kDrawThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    return CLASP_OK;
+    return launch_draw(a, st);
 }
 
 int clasp_dp_select_window(clasp_ctx* ctx, const float* states, size_t layer_stride, int pos, int M, int layer_lo,

@@ -3,12 +3,10 @@
 // 3.6 of the paper) read afterwards. With C rows per pass the GEMMs do C flop per weight byte, beyond the ridge of the
 // part (~310) from a few hundred rows on, so unlike the decode-time kernels these are organised around the matrix
 // cores and around getting operands to them:
-//   * prefill_gemm256_kernel: 256 x 256 workgroup tiles, 4 x 2 wavefronts with 64 x 128 accumulators; both operands
-//     are stored in MFMA fragment order already (weights as packed for the decode kernels, activations as the operand
-//     planes every producer writes), so staging is a copy of whole KiB fragments, done by direct global -> LDS loads
-//     into a ring of three or four stages.
-//   * prefill_gemm_kernel: 128 x 128 or 64 x 128 tiles staged through registers, for the q/k/v projection and for
-//     passes too short for the big tile; prefill_reduce_kernel finishes a K-split of very short passes.
+//   * prefill_ring_kernel: workgroup tiles of 32 x 128 to 256 x 256; both operands are stored in MFMA fragment order
+//     already (weights as packed for the decode kernels, activations as the operand planes every producer writes), so
+//     staging is a copy of whole KiB fragments, done by direct global -> LDS loads into a ring of three to five stages.
+//   * prefill_reduce_kernel: finishes the projections onto d_model of passes that split their contraction.
 //   * prefill_attn_lds_kernel / prefill_attn_kernel: causal flash attention over the fragment-order cache; a wavefront
 //     owns two tiles of 16 queries (row x head of one KV group); long prefixes share each 32-key block among the eight
 //     wavefronts of a workgroup through a ring of LDS stages, short ones are read by every wavefront itself.
@@ -30,10 +28,11 @@ struct PrefillGemmArgs {
     GemmArgs g;          // W, tile_end, A, n_rows, N, K, R, out/ldo, resid/ldr, next_op, next_gain, next_ss, qkv
     const float* rstd;   // [n_rows] 1/rms of the input rows (projections that follow a norm), else null
     int ld_ss;           // row capacity of next_ss: next_ss[tile][ld_ss]
-    // kEpiPartial (prefill_gemm_kernel with gridDim.y = k_split > 1): slice y of the contraction leaves its raw sums in
-    // g.out + y * slab ([rows][g.ldo]); prefill_reduce_kernel adds the slices in order and runs the residual epilogue
-    int k_split;
+    // kEpiPartial (gridDim.y slices of the contraction): slice y leaves its raw sums in g.out + y * slab ([rows][g.ldo]);
+    // prefill_reduce_kernel adds the slices in order and runs the residual epilogue
     size_t slab;
+    float* next_rstd;    // kEpiResid: [n_rows] 1/rms of the output rows
+    float inv_dim, eps;  // ... of which it is made
     int op_f16;          // format of next_op: one fp16 plane (passes that run on fp16 MFMAs) or the bf16 hi / lo planes
 };
 
@@ -62,20 +61,66 @@ __global__ __launch_bounds__(1024) void prefill_rstd_kernel(const float* ss, int
     }
 }
 
-// Embedding gather for a chunk: h_0, the first layer's operand (times its norm gains) and sum-of-squares partials.
-// Grid (rows, ceil(d / 256)).
-__global__ __launch_bounds__(256) void prefill_embed_kernel(const int32_t* tokens, const bf16* table, int vocab, int d,
-                                                            float* h, void* op, int R, const float* gain, float* ss,
-                                                            int ld_ss, int op_f16) {
-    const int row = blockIdx.x, c = blockIdx.y * 256 + threadIdx.x;
-    if (c >= d) return;
-    int tok = tokens[row];
-    tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
-    const float v = from_bf16(table[(size_t)tok * d + c]);
-    h[(size_t)row * d + c] = v;
-    store_operand_fmt(op, R, row, c, v * gain[c], op_f16);
-    const float sq = sum16(v * v);
-    if ((c & 15) == 0) ss[(size_t)(c >> 4) * ld_ss + row] = sq;
+// How the two row-wise kernels below (embedding gather, sum of K-slices) share rows and columns out. Each handles whole rows,
+// so that it can leave their 1/rms, 4 columns per thread and step. bf16 passes: a workgroup per row, whose operand pieces
+// are 64 contiguous bytes per k-step and plane. fp16 passes: eight rows per workgroup of sixteen wavefronts, a wavefront
+// taking eight rows x 32 columns at a time, because the fp16 plane interleaves the rows in 16-byte pieces and only eight
+// rows fill a 128-byte line (a workgroup per row wrote eighths of lines from eight XCDs: 4096 rows gathered in 92 us, 28
+// us now; 1100 rows: two slices summed in 24 us, three in 24 us now, 4.5 TB/s).
+template <bool F16>
+struct RowBlock {
+    static constexpr int kRows = F16 ? 8 : 1, kThreads = F16 ? 1024 : 256;
+    static constexpr int kStep = kThreads / kRows;  // chunks of four columns a row advances by
+    int row, chunk;
+    __device__ RowBlock() {
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        row = F16 ? blockIdx.x * 8 + (lane >> 3) : blockIdx.x;
+        chunk = F16 ? wave * 8 + (lane & 7) : threadIdx.x;
+    }
+    // sum over the row's threads of v, in the row's first thread (chunk 0); red: kThreads / 64 * kRows floats
+    __device__ float row_sum(float v, float* red) const {
+        if constexpr (!F16) return block_sum(v, red);
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        v += __shfl_xor(v, 1);
+        v += __shfl_xor(v, 2);
+        v += __shfl_xor(v, 4);
+        if ((lane & 7) == 0) red[wave * 8 + (lane >> 3)] = v;
+        __syncthreads();
+        float t = 0.f;
+        for (int w = 0; w < kThreads / 64; ++w) t += red[w * 8 + (lane >> 3)];
+        return t;
+    }
+};
+
+// Embedding gather for a chunk: h_0, the first layer's operand (times its norm gains) and 1/rms.
+template <bool F16>
+__global__ __launch_bounds__(RowBlock<F16>::kThreads) void prefill_embed_kernel(const int32_t* tokens, const bf16* table, int vocab,
+                                                                                int d, int n_rows, float* h, void* op, int R,
+                                                                                const float* gain, float* rstd, float eps) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    __shared__ float red[RowBlock<F16>::kThreads / 64 * RowBlock<F16>::kRows];
+    const RowBlock<F16> b;
+    const bool live = b.row < n_rows;
+    float sq = 0.f;
+    if (live) {
+        int tok = tokens[b.row];
+        tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
+        const bf16x4* src = reinterpret_cast<const bf16x4*>(table + (size_t)tok * d);  // d % 32 == 0
+        f32x4* dst = reinterpret_cast<f32x4*>(h + (size_t)b.row * d);
+#pragma unroll 4
+        for (int c = b.chunk; c < d / 4; c += b.kStep) {
+            const bf16x4 x = src[c];
+            const f32x4 gn = reinterpret_cast<const f32x4*>(gain)[c];
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = from_bf16(x[e]);
+            dst[c] = v;
+            store_operand4_fmt(op, R, b.row, c * 4, v * gn, F16);
+            sq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+        }
+    }
+    sq = b.row_sum(sq, red);
+    if (live && b.chunk == 0) rstd[b.row] = 1.0f / sqrtf(sq / d + eps);
 }
 
 // The GEMMs below multiply with the weight fragment as the MFMA's first operand and the activation fragment as its
@@ -227,14 +272,7 @@ __device__ __forceinline__ void prefill_epilogue_all(const PrefillGemmArgs& p, i
     }
 }
 
-constexpr int kPrefillRM = 4;                      // 16-row tiles per wavefront (2 in the small-tile variant)
-constexpr int kPrefillRows = 2 * kPrefillRM * 16;  // rows of the 128-row workgroup tile; chunk sizes are multiples of it
-
-// D = k-steps a stage is requested ahead of its use (register sets in flight); D + 1 LDS stages
-template <int RM, int RN, int D, bool F16 = false>
-constexpr size_t prefill_gemm_lds_bytes() {
-    return (size_t)(D + 1) * (2 * (F16 ? 1 : 2) * RM + 2 * RN) * 1024;
-}
+constexpr int kPrefillRows = 128;  // chunk sizes are multiples of it
 
 // acc += (activation fragment a) x (weight fragment b) on the matrix cores, operands bf16 or fp16 as the pass runs
 template <bool F16>
@@ -244,182 +282,62 @@ __device__ __forceinline__ f32x4 prefill_mma(const u32x4& a, const u32x4& b, con
     else return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(b), as_bf16x8(a), acc, 0, 0, 0);
 }
 
-// Workgroup = 2 x 2 wavefronts; wavefront (wm, wn) accumulates row tiles wm*RM .. +RM-1 times feature tiles wn*RN ..
-// +RN-1 of the workgroup tile (RM = 4: 128 rows; RM = 2: 64 rows, for passes so short that 128-row tiles would leave
-// CUs without a workgroup). Per k-step the workgroup stages 4*RM activation fragments (row tiles x hi/lo) and 2*RN weight
-// fragments of 1 KiB each: requested into registers at the top of a k-step, written to a free LDS stage after the
-// MFMAs of the D-th k-step from there (D register sets alternate, D + 1 LDS stages), one barrier per k-step. Two
-// workgroups share a CU (<= 256 registers per lane, <= 80 KiB of LDS each), so one computes while the other waits for
-// LDS, memory or its barrier; WPS = wavefronts per SIMD the register budget is cut for (3 with RN = 4, D = 1: 48 KiB of
-// LDS and 152 registers, three workgroups per CU).
-// Workgroups are numbered so that the ones resident on an XCD at the same time share weight columns: the XCD's L2
-// then sees each weight fragment from HBM once and serves the sibling row blocks.
-template <int EPI, int RM, int RN, int D, int WPS, bool F16 = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void prefill_gemm_kernel(PrefillGemmArgs p) {
-    constexpr int NSTAGE = D + 1, ROWS = 2 * RM * 16;
-    constexpr int NP = F16 ? 1 : 2;  // planes of an activation fragment: fp16, or bf16 hi + lo
-    constexpr int A_FR = 2 * NP * RM, B_FR = 2 * RN, FR = A_FR + B_FR, NL = FR / 4;
-    static_assert(FR % 4 == 0 && (D == 1 || D == 2), "fragments are dealt to four wavefronts");
-    extern __shared__ u32x4 prefill_lds[];  // [NSTAGE][FR][64]
+// Sum of the SPLIT slices a split contraction left behind, in slice order, plus the residual epilogue: output row, next
+// operand and 1/rms of the row. All loads of a thread's chunk are requested together. 300 rows of 4096 columns and four
+// slices: 11.3 us with one column per thread and the 1/rms left to a kernel of its own (4.6 us more), 9.2 us now.
+template <int SPLIT, bool F16>
+__global__ __launch_bounds__(RowBlock<F16>::kThreads) void prefill_reduce_kernel(PrefillGemmArgs p, const float* parts) {
+    __shared__ float red[RowBlock<F16>::kThreads / 64 * RowBlock<F16>::kRows];
     const GemmArgs& g = p.g;
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, wm = w >> 1, wn = w & 1;
-    const int KS_all = g.K >> 5, n_tiles = g.N >> 4;
-    // this workgroup's slice of the contraction (all of it unless gridDim.y > 1)
-    const int ks0 = (int)(((long long)KS_all * blockIdx.y) / gridDim.y), KS = (int)(((long long)KS_all * (blockIdx.y + 1)) / gridDim.y) - ks0;
-    const int nrb = (g.R * 16 + ROWS - 1) / ROWS, ncb = (n_tiles + B_FR - 1) / B_FR;
-    // block id -> (row block, column block): ids congruent mod 8 run on one XCD; give each XCD a contiguous range
-    const int total = nrb * ncb, per_xcd = (total + 7) >> 3;
-    const int pid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
-    if (pid >= total) return;
-    const int rb = pid % nrb, cb = pid / nrb;
-
-    // loader role: fragments w, w + 4, .. of the stage
-    const u32x4* src[NL];
-    size_t step[NL];
+    const RowBlock<F16> b;
+    const bool live = b.row < g.n_rows;
+    float sq = 0.f;
+    if (live) {
+        const f32x4* resid = reinterpret_cast<const f32x4*>(g.resid + (size_t)b.row * g.ldr);
+        const f32x4* slices = reinterpret_cast<const f32x4*>(parts + (size_t)b.row * g.ldo);
+        f32x4* out = reinterpret_cast<f32x4*>(g.out + (size_t)b.row * g.ldo);
+        const size_t slab = p.slab / 4;
+#pragma unroll 2
+        for (int c = b.chunk; c < g.N / 4; c += b.kStep) {
+            f32x4 v = resid[c], part[SPLIT];
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-        const int f = w + 4 * j;
-        if (f < A_FR) {  // activation fragment: row tile f/NP, plane f%NP; fetched in the order the MFMA lanes want it
-            const int rg = min(rb * (2 * RM) + f / NP, g.R - 1);
-            // bf16 planes are row-major (lane q*16 + r takes row r, 16-byte piece q); the fp16 plane is in lane order
-            src[j] = reinterpret_cast<const u32x4*>(g.A) + ((size_t)rg * NP + f % NP) * 64 +
-                     (F16 ? lane : (lane & 15) * 4 + (lane >> 4));
-            step[j] = (size_t)g.R * NP * 64;
-        } else {
-            const int tile = min(cb * B_FR + (f - A_FR), n_tiles - 1);
-            int mi = 0, tl = tile;
-            if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
-            if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
-            src[j] = reinterpret_cast<const u32x4*>(g.W[mi]) + (size_t)tl * KS_all * 64 + lane;
-            step[j] = 64;
-        }
-        src[j] += (size_t)ks0 * step[j];
-    }
-    auto issue = [&](u32x4 (&r)[NL]) {
+            for (int k = 0; k < SPLIT; ++k) part[k] = slices[k * slab + c];
+            const f32x4 gain = reinterpret_cast<const f32x4*>(g.next_gain)[c];
 #pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            r[j] = *src[j];
-            src[j] += step[j];
-        }
-    };
-    auto commit = [&](const u32x4 (&r)[NL], int buf) {
-#pragma unroll
-        for (int j = 0; j < NL; ++j) prefill_lds[((size_t)buf * FR + (w + 4 * j)) * 64 + lane] = r[j];
-    };
-
-    f32x4 acc[RM][RN];
-#pragma unroll
-    for (int i = 0; i < RM; ++i)
-#pragma unroll
-        for (int j = 0; j < RN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto compute = [&](int buf) {
-        const u32x4* L = prefill_lds + (size_t)buf * FR * 64 + lane;
-        u32x4 bf[RN];
-#pragma unroll
-        for (int j = 0; j < RN; ++j) bf[j] = L[(A_FR + wn * RN + j) * 64];
-        // the next row tile's fragment(s) are requested before this tile's MFMAs are issued (the scheduling fences
-        // keep the compiler from sinking the reads below them): LDS latency hides behind the MFMAs
-        u32x4 a[NP];
-#pragma unroll
-        for (int h = 0; h < NP; ++h) a[h] = L[(wm * RM * NP + h) * 64];
-#pragma unroll
-        for (int i = 0; i < RM; ++i) {
-            u32x4 c[NP];
-#pragma unroll
-            for (int h = 0; h < NP; ++h) c[h] = a[h];
-            if (i + 1 < RM) {
-#pragma unroll
-                for (int h = 0; h < NP; ++h) a[h] = L[((wm * RM + i + 1) * NP + h) * 64];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int h = 0; h < NP; ++h)
-#pragma unroll
-                for (int j = 0; j < RN; ++j) acc[i][j] = prefill_mma<F16>(c[h], bf[j], acc[i][j]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
-    // stage s is requested at the top of k-step s - D, committed to LDS stage s % (D + 1) after the MFMAs of k-step
-    // s - 1 (the barrier that ended k-step s - 2 freed that stage) and consumed in k-step s
-    u32x4 r0[NL], r1[D == 2 ? NL : 1];
-    issue(r0);
-    commit(r0, 0);
-    if constexpr (D == 1) {
-        __syncthreads();
-        for (int s = 0; s < KS; ++s) {
-            if (s + 1 < KS) issue(r0);
-            compute(s & 1);
-            if (s + 1 < KS) commit(r0, (s + 1) & 1);
-            __syncthreads();
-        }
-    } else {
-        if (KS > 1) issue(r0);  // stage 1
-        __syncthreads();
-        int buf = 0;
-        auto iteration = [&](int s, u32x4 (&cur)[NL], u32x4 (&nxt)[NL]) {  // cur holds stage s + 1, nxt is free
-            if (s + 2 < KS) issue(nxt);
-            compute(buf);
-            buf = buf == NSTAGE - 1 ? 0 : buf + 1;
-            if (s + 1 < KS) commit(cur, buf);
-            __syncthreads();
-        };
-        for (int s = 0; s < KS; s += 2) {
-            iteration(s, r0, r1);
-            if (s + 1 < KS) iteration(s + 1, r1, r0);
+            for (int k = 0; k < SPLIT; ++k) v += part[k];
+            out[c] = v;
+            store_operand4_fmt(g.next_op, g.R, b.row, c * 4, v * gain, F16);
+            sq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
         }
     }
-
-    prefill_epilogue_all<EPI, RM, RN>(p, rb * (2 * RM) + wm * RM, cb * B_FR + wn * RN, n_tiles, lane, acc);
+    sq = b.row_sum(sq, red);
+    if (live && b.chunk == 0) p.next_rstd[b.row] = 1.0f / sqrtf(sq * p.inv_dim + p.eps);
 }
 
-// Sum of the k_split slices a split contraction left behind, in slice order, plus the residual epilogue (output, next
-// operand, sum-of-squares partials). Grid (rows, ceil(N / 256)), one column per thread.
-__global__ __launch_bounds__(256) void prefill_reduce_kernel(PrefillGemmArgs p, const float* parts) {
-    const GemmArgs& g = p.g;
-    const int row = blockIdx.x, c = blockIdx.y * 256 + threadIdx.x;
-    if (c >= g.N) return;  // N % 16 == 0: a 16-column tile is all in or out
-    float v = g.resid[(size_t)row * g.ldr + c];
-    for (int s = 0; s < p.k_split; ++s) v += parts[(size_t)s * p.slab + (size_t)row * g.ldo + c];
-    g.out[(size_t)row * g.ldo + c] = v;
-    if (g.next_op) store_operand_fmt(g.next_op, g.R, row, c, v * (g.next_gain ? g.next_gain[c] : 1.0f), p.op_f16);
-    const float sq = sum16(v * v);
-    if (g.next_ss && (c & 15) == 0) g.next_ss[(size_t)(c >> 4) * p.ld_ss + row] = sq;
-}
-
-// ---- 256 x 256 tile fed by direct global -> LDS loads ---------------------------------------------------------------
-// What binds the kernel above is operand delivery: a 128 x 256 tile pulls 32 KiB per k-step through L2 for 4 MFLOP, most
-// of it with Infinity-Cache / HBM latency, and registers + LDS keep only one or two k-steps in flight. Here a workgroup
-// of 4 x 2 wavefronts (64 x 128 accumulators each) owns a 256 x 256 tile (48 KiB per k-step for 8 MFLOP), and the
-// fragments go straight from global memory into a ring of three LDS stages with global_load_lds_dwordx4 (per lane a
-// global address, destination = wave-uniform LDS base + lane * 16, which is exactly a fragment): no staging registers,
-// two k-steps (96 KiB per CU) in flight while the third is consumed. The loads are written as inline assembly
-// because their completion has to be awaited stage by stage (s_waitcnt vmcnt(N): the N loads of the later stages may
-// stay in flight); nothing else in the loop touches global memory, and the counter is drained before the epilogue.
-// (The same loop on 32 x 32 x 16 MFMAs, whose operands a lane can gather from two neighbouring fragments, measured 12 %
-// slower.)
-// With fp16 operands a k-step is 16 + 16 fragments (32 KiB) and the ring has four stages: one being read into registers
-// a k-step ahead of its MFMAs, three in flight (see the loop).
-constexpr int kPrefillBigRows = 256;
+// ---- workgroup tiles fed by direct global -> LDS loads ---------------------------------------------------------------
+// What bounds a pass of a few hundred or thousand rows is operand delivery and how its tiles divide over the CUs: a 128 x
+// 128 tile whose operands go through registers pulls 24-32 KiB per k-step with only 64-96 KiB in flight per CU, and a
+// projection onto d_model makes 160-288 such workgroups for 256 CUs. Here the fragments of a workgroup tile (WM x WN
+// wavefronts, RM x RN accumulator tiles of 16 x 16 each) go straight from global memory into a ring of LDS stages with
+// global_load_lds_dwordx4 (per lane a global address, destination = wave-uniform LDS base + lane * 16, which is exactly
+// a fragment): no staging registers, all stages but one in flight (72-160 KiB per CU), and the launcher picks among tiles
+// of 32 x 128 to 256 x 256 the one whose rounds of CUs are cheapest for the launch at hand (clasp_api.hip). The loads are
+// written as inline assembly because their completion has to be awaited stage by stage (s_waitcnt vmcnt(N): the N loads
+// of the later stages may stay in flight); nothing else in the loop touches global memory, and the counter is drained
+// before the epilogue.
+// Measured at the 8B shape, register-staged or fixed 256 x 256 tiles -> now: 300 rows (bf16, hi + lo) gate/up 198 -> 129-141
+// us, q/k/v 93 -> 48, down 93 -> 74, o 32 -> 26; 1100 rows (fp16) gate/up 330 -> 276, down 307 -> 126, o 111 -> 75, q/k/v 97
+// -> 83. From about 3000 rows on every tile of this family takes the same time to 1 % (4096 rows: gate/up 805-880 us
+// depending on the card, 1.09-1.19 PFLOP/s, the rate torch's matrix product reaches on it): the card's power limit, not
+// the schedule, is what is left there.
 #ifndef CLASP_PREFILL_GROUP_ROWS
 #define CLASP_PREFILL_GROUP_ROWS 4
 #endif
-#ifndef CLASP_PREFILL_REGPIPE
-#define CLASP_PREFILL_REGPIPE 1
-#endif
-#ifndef CLASP_PREFILL_F16_STAGES
-#define CLASP_PREFILL_F16_STAGES 4
-#endif
-template <bool F16>
-constexpr int prefill_big_stages() { return F16 ? CLASP_PREFILL_F16_STAGES : 3; }
-// RN = feature tiles per wavefront: 8 (256 columns per workgroup) or 6 (192 columns: the q/k/v projection, whose 384
-// feature tiles make 512 workgroups = two full rounds of CUs that way, and whose epilogue needs the registers)
-template <bool F16, int RN = 8>
-constexpr int prefill_big_frags() {  // activation + weight fragments per k-step, padded to eight wavefronts' equal shares
-    return (4 * kPrefillRM * (F16 ? 1 : 2) + 2 * RN + 7) / 8 * 8;
+template <bool F16, int WM, int WN, int RM, int RN>
+constexpr int prefill_ring_frags() {  // activation + weight fragments per k-step, padded to the wavefronts' equal shares
+    constexpr int NW = WM * WN;
+    return (WM * RM * (F16 ? 1 : 2) + WN * RN + NW - 1) / NW * NW;
 }
-template <bool F16, int RN = 8>
-constexpr size_t prefill_big_lds() { return (size_t)prefill_big_stages<F16>() * prefill_big_frags<F16, RN>() * 1024; }
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {  // all but the newest N vector-memory operations of this wavefront are done
@@ -453,22 +371,25 @@ __device__ __forceinline__ void load_to_lds_16(const void* uniform_base, unsigne
     asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(base), "v"(lane_offset), "s"(sb) : "memory");
 }
 
-template <int EPI, bool F16 = false, int RN = 8>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void prefill_gemm256_kernel(PrefillGemmArgs p) {
-    constexpr int NP = F16 ? 1 : 2;  // planes of an activation fragment: fp16, or bf16 hi + lo
+template <int EPI, bool F16, int WM, int WN, int RM, int RN, int NSTAGE, int WPS>
+__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(WPS, WPS))) void prefill_ring_kernel(PrefillGemmArgs p) {
+    constexpr int NW = WM * WN, NP = F16 ? 1 : 2;  // planes of an activation fragment: fp16, or bf16 hi + lo
     // FR: slots of a stage (1 KiB each); the last FR - A_FR - B_FR of them are padding that receives copies of the last
     // weight fragment, so that every wavefront issues the same number of loads per stage
-    constexpr int RM = kPrefillRM, A_FR = 4 * RM * NP, B_FR = 2 * RN, FR = prefill_big_frags<F16, RN>(), NL = FR / 8;
-    constexpr int NSTAGE = prefill_big_stages<F16>(), AHEAD = NSTAGE - 1;
-    static_assert(FR >= A_FR + B_FR && FR % 8 == 0, "fragments are dealt to eight wavefronts");
-    static_assert((F16 && CLASP_PREFILL_REGPIPE) || AHEAD == 2 || AHEAD == 3,
-                  "the waits of the plain loop are written out for two or three stages in flight");
+    constexpr int A_FR = WM * RM * NP, B_FR = WN * RN, FR = prefill_ring_frags<F16, WM, WN, RM, RN>(), NL = FR / NW;
+    static_assert(NSTAGE >= 3 && NSTAGE <= 5, "wait_all_but_stages handles up to four stages in flight");
     extern __shared__ u32x4 prefill_lds[];  // [NSTAGE][FR][64]
     const GemmArgs& g = p.g;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
-    const int KS = g.K >> 5, n_tiles = g.N >> 4;
-    const int nrb = (g.R * 16 + kPrefillBigRows - 1) / kPrefillBigRows, ncb = (n_tiles + B_FR - 1) / B_FR;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w / WN, wn = w % WN;
+    const int KS_all = g.K >> 5, n_tiles = g.N >> 4;
+    // this workgroup's slice of the contraction (kEpiPartial: one of gridDim.y, else all of it)
+    int ks0 = 0, KS = KS_all;
+    if constexpr (EPI == kEpiPartial) {
+        ks0 = (int)((unsigned)KS_all * blockIdx.y / gridDim.y);
+        KS = (int)((unsigned)KS_all * (blockIdx.y + 1) / gridDim.y) - ks0;
+    }
+    const int nrb = (g.R + WM * RM - 1) / (WM * RM), ncb = (n_tiles + B_FR - 1) / B_FR;
     const int total = nrb * ncb, per_xcd = (total + 7) >> 3;
     const int pid = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (pid >= total) return;
@@ -478,19 +399,19 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int grp = pid / (GR * ncb), in_grp = pid - grp * (GR * ncb), rows_grp = min(GR, nrb - grp * GR);
     const int rb = grp * GR + in_grp % rows_grp, cb = in_grp / rows_grp;
 
-    // this wavefront's fragments w, w + 8, .. of a stage: a wave-uniform address each (kept in scalar registers) plus
+    // this wavefront's fragments w, w + NW, .. of a stage: a wave-uniform address each (kept in scalar registers) plus
     // one of two per-lane offsets (activation fragments are fetched in the order the MFMA lanes want them)
-    static_assert(A_FR % 8 == 0, "a wavefront's j-th fragment is an activation fragment in all wavefronts or in none");
     const char* src[NL];
     size_t step[NL];
-    // bf16 planes are row-major (lane q*16 + r takes row r, 16-byte piece q); the fp16 plane is in lane order
-    const unsigned lane_off_b = (unsigned)lane * 16;
-    const unsigned lane_off_a = F16 ? lane_off_b : (unsigned)((lane & 15) * 4 + (lane >> 4)) * 16;
+    // bf16 planes are row-major (lane q*16 + r takes row r, 16-byte piece q); everything else is in lane order
+    unsigned lane_off[F16 ? 1 : NL];
+    lane_off[0] = (unsigned)lane * 16;
 #pragma unroll
     for (int j = 0; j < NL; ++j) {
-        const int f = w + 8 * j;
+        const int f = w + NW * j;
+        if constexpr (!F16) lane_off[j] = (unsigned)(f < A_FR ? (lane & 15) * 4 + (lane >> 4) : lane) * 16;
         if (f < A_FR) {
-            const int rg = min(rb * (A_FR / NP) + f / NP, g.R - 1);
+            const int rg = min(rb * (WM * RM) + f / NP, g.R - 1);
             src[j] = reinterpret_cast<const char*>(g.A) + ((size_t)rg * NP + f % NP) * 1024;
             step[j] = (size_t)g.R * NP * 1024;
         } else {
@@ -498,15 +419,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             int mi = 0, tl = tile;
             if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
             if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
-            src[j] = reinterpret_cast<const char*>(g.W[mi]) + (size_t)tl * KS * 1024;
+            src[j] = reinterpret_cast<const char*>(g.W[mi]) + (size_t)tl * KS_all * 1024;
             step[j] = 1024;
         }
+        if constexpr (EPI == kEpiPartial) src[j] += (size_t)ks0 * step[j];
     }
     const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)prefill_lds);
     auto issue = [&](int buf) {  // this wavefront's NL fragments of the next stage in line
 #pragma unroll
         for (int j = 0; j < NL; ++j) {
-            load_to_lds_16(src[j], 8 * j < A_FR ? lane_off_a : lane_off_b, lds_base + (unsigned)((buf * FR + w + 8 * j) * 1024));
+            load_to_lds_16(src[j], lane_off[F16 ? 0 : j], lds_base + (unsigned)((buf * FR + w + NW * j) * 1024));
             src[j] += step[j];
         }
     };
@@ -516,118 +438,83 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int i = 0; i < RM; ++i)
 #pragma unroll
         for (int j = 0; j < RN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto compute = [&](int buf) {
+    // Two sets of fragment registers: the fragments of stage s + 1 are read from LDS while the MFMAs of stage s run from
+    // registers, so LDS reads and matrix cores overlap inside a wavefront instead of alternating in lockstep across the
+    // workgroup behind the barrier. A stage's LDS slot is free once every wavefront holds it in registers (the barrier
+    // of the k-step that multiplies it), so all NSTAGE slots are in use: one being read, the others in flight.
+    constexpr int NA = RM * NP;  // activation fragments of a wavefront: row tile t / NP, plane t % NP
+    u32x4 a0[NA], b0[RN], a1[NA], b1[RN];
+#pragma unroll
+    for (int t = 0; t < NSTAGE; ++t)
+        if (t < KS) issue(t);
+    wait_all_but_stages<NL>(min(KS, NSTAGE) - 1);  // own loads of stage 0 have landed
+    __syncthreads();
+    {
+        const u32x4* L = prefill_lds + lane;
+#pragma unroll
+        for (int j = 0; j < RN; ++j) b0[j] = L[(A_FR + wn * RN + j) * 64];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a0[i] = L[(wm * NA + i) * 64];
+    }
+    int buf = 0;  // LDS slot of stage s
+    constexpr int NM = NA * RN;
+    auto mma_one = [&](const u32x4 (&a)[NA], const u32x4 (&b)[RN], int m) {  // m-th MFMA of a k-step: row tile by row tile, hi then lo
+        const int t = m / RN, j = m % RN;
+        acc[t / NP][j] = prefill_mma<F16>(a[t], b[j], acc[t / NP][j]);
+    };
+    auto mma = [&](const u32x4 (&a)[NA], const u32x4 (&b)[RN]) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) mma_one(a, b, m);
+    };
+    // k-step s < KS - 1: stage s + 1 goes to the other register set while stage s is multiplied. Every path through
+    // it reads before it multiplies: a k-step that could skip the reads would make the compiler wait for them in
+    // front of the MFMAs on the common path as well (the wait counters are merged where paths meet).
+    auto kstep = [&](int s, const u32x4 (&ca)[NA], const u32x4 (&cb_)[RN], u32x4 (&na)[NA], u32x4 (&nb)[RN]) {
+        const int later = KS - 1 - s;
+        // own loads of stage s + 1 have landed; stages s + 2 .. s + NSTAGE - 1 (where they exist) may stay in flight
+        wait_all_but_stages<NL>(min(later - 1, NSTAGE - 2));
+        __syncthreads();  // everybody's have, and every wavefront has stage s in registers
+        if (s + NSTAGE < KS) issue(buf);
+        buf = buf == NSTAGE - 1 ? 0 : buf + 1;
+        // the reads of stage s + 1 are spread between the MFMAs of stage s (pinned by scheduling fences): issued in one
+        // burst by all wavefronts after the barrier they would fill the LDS queue, and a wavefront whose read is not
+        // accepted cannot issue the MFMAs behind it
         const u32x4* L = prefill_lds + (size_t)buf * FR * 64 + lane;
-        u32x4 bf[RN];
+        constexpr int NR = NA + RN;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < RN; ++j) bf[j] = L[(A_FR + wn * RN + j) * 64];
-        u32x4 a[NP];
+        for (int t = 0; t < NR; ++t) {
+            if (t < RN) nb[t] = L[(A_FR + wn * RN + t) * 64];
+            else na[t - RN] = L[(wm * NA + t - RN) * 64];
 #pragma unroll
-        for (int h = 0; h < NP; ++h) a[h] = L[(wm * RM * NP + h) * 64];
-#pragma unroll
-        for (int i = 0; i < RM; ++i) {
-            u32x4 c[NP];
-#pragma unroll
-            for (int h = 0; h < NP; ++h) c[h] = a[h];
-            if (i + 1 < RM) {
-#pragma unroll
-                for (int h = 0; h < NP; ++h) a[h] = L[((wm * RM + i + 1) * NP + h) * 64];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int h = 0; h < NP; ++h)
-#pragma unroll
-                for (int j = 0; j < RN; ++j) acc[i][j] = prefill_mma<F16>(c[h], bf[j], acc[i][j]);
+            for (int m = t * NM / NR; m < (t + 1) * NM / NR; ++m) mma_one(ca, cb_, m);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-
-    if constexpr (F16 && CLASP_PREFILL_REGPIPE) {
-        // fp16 operands leave room for a second set of fragment registers: the fragments of stage s + 1 are read from
-        // LDS while the MFMAs of stage s run from registers, so LDS reads and matrix cores overlap inside a wavefront
-        // instead of alternating in lockstep across the workgroup behind the barrier. A stage's LDS slot is free once
-        // every wavefront holds it in registers (the barrier of the k-step that multiplies it), so all NSTAGE slots
-        // are in use: one being read, the others in flight.
-        static_assert(NSTAGE >= 3 && NSTAGE <= 5, "wait_all_but_stages handles up to four stages in flight");
-        u32x4 a0[RM], b0[RN], a1[RM], b1[RN];
-        auto fetch = [&](int buf, u32x4 (&a)[RM], u32x4 (&b)[RN]) {
-            const u32x4* L = prefill_lds + (size_t)buf * FR * 64 + lane;
+    // Pairs of k-steps alternate the two register sets, and the last pair ends without a read. An odd k-step goes first
+    // (as one of two possible ends it made the compiler spill accumulators); if it is the only one, what it reads is not
+    // used.
+    int s = 0;
+    if (KS & 1) {
+        kstep(0, a0, b0, a1, b1);
 #pragma unroll
-            for (int j = 0; j < RN; ++j) b[j] = L[(A_FR + wn * RN + j) * 64];
+        for (int i = 0; i < NA; ++i) a0[i] = a1[i];
 #pragma unroll
-            for (int i = 0; i < RM; ++i) a[i] = L[(wm * RM + i) * 64];
-        };
-#pragma unroll
-        for (int t = 0; t < NSTAGE; ++t)
-            if (t < KS) issue(t);
-        wait_all_but_stages<NL>(min(KS, NSTAGE) - 1);  // own loads of stage 0 have landed
-        __syncthreads();
-        fetch(0, a0, b0);
-        int buf = 0;  // LDS slot of stage s
-        auto mma = [&](const u32x4 (&a)[RM], const u32x4 (&b)[RN]) {
-#pragma unroll
-            for (int i = 0; i < RM; ++i)
-#pragma unroll
-                for (int j = 0; j < RN; ++j) acc[i][j] = prefill_mma<true>(a[i], b[j], acc[i][j]);
-        };
-        // k-step s < KS - 1: stage s + 1 goes to the other register set while stage s is multiplied. Every path through
-        // it reads before it multiplies: a k-step that could skip the reads would make the compiler wait for them in
-        // front of the MFMAs on the common path as well (the wait counters are merged where paths meet).
-        auto kstep = [&](int s, const u32x4 (&ca)[RM], const u32x4 (&cb_)[RN], u32x4 (&na)[RM], u32x4 (&nb)[RN]) {
-            const int later = KS - 1 - s;
-            // own loads of stage s + 1 have landed; stages s + 2 .. s + NSTAGE - 1 (where they exist) may stay in flight
-            wait_all_but_stages<NL>(min(later - 1, NSTAGE - 2));
-            __syncthreads();  // everybody's have, and every wavefront has stage s in registers
-            if (s + NSTAGE < KS) issue(buf);
-            buf = buf == NSTAGE - 1 ? 0 : buf + 1;
-            // the RM + RN reads of stage s + 1 are spread between the RM * RN MFMAs of stage s (two or three MFMAs after
-            // each read, pinned by scheduling fences): issued in one burst by all eight wavefronts after the barrier they
-            // would fill the LDS queue, and a wavefront whose read is not accepted cannot issue the MFMAs behind it
-            const u32x4* L = prefill_lds + (size_t)buf * FR * 64 + lane;
-            constexpr int NR = RM + RN, NM = RM * RN;
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < NR; ++t) {
-                if (t < RN) nb[t] = L[(A_FR + wn * RN + t) * 64];
-                else na[t - RN] = L[(wm * RM + t - RN) * 64];
-#pragma unroll
-                for (int m = t * NM / NR; m < (t + 1) * NM / NR; ++m)
-                    acc[m / RN][m % RN] = prefill_mma<true>(ca[m / RN], cb_[m % RN], acc[m / RN][m % RN]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        // KS is even (the launcher sends other contractions to the smaller tiles): pairs of k-steps alternate the two
-        // register sets, and the last pair ends without a read
-        for (int s = 0; s + 2 < KS; s += 2) {
-            kstep(s, a0, b0, a1, b1);
-            kstep(s + 1, a1, b1, a0, b0);
-        }
-        kstep(KS - 2, a0, b0, a1, b1);
-        mma(a1, b1);
-    } else {
-    // stage s lives in LDS stage s % NSTAGE; it is requested AHEAD k-steps before its use, right after the barrier that
-    // tells that every wavefront has finished reading the stage it replaces
-#pragma unroll
-    for (int t = 0; t < AHEAD; ++t)
-        if (t < KS) issue(t);
-    int buf = 0;
-    for (int s = 0; s < KS; ++s) {
-        // own loads of stage s have landed: the stages requested after it (at most AHEAD - 1, fewer at the end) may
-        // stay in flight
-        const int later = KS - 1 - s;
-        if (later >= AHEAD - 1) wait_vmcnt<(AHEAD - 1) * NL>();
-        else if (AHEAD == 3 && later == 1) wait_vmcnt<NL>();
-        else wait_vmcnt<0>();
-        __syncthreads();  // everybody's have, and stage s - 1 is no longer read
-        if (s + AHEAD < KS) issue(buf == 0 ? NSTAGE - 1 : buf - 1);  // (s + AHEAD) % NSTAGE
-        compute(buf);
-        buf = buf == NSTAGE - 1 ? 0 : buf + 1;
+        for (int j = 0; j < RN; ++j) b0[j] = b1[j];
+        s = 1;
     }
+    for (; s + 2 < KS; s += 2) {
+        kstep(s, a0, b0, a1, b1);
+        kstep(s + 1, a1, b1, a0, b0);
+    }
+    if (s < KS) {
+        kstep(s, a0, b0, a1, b1);
+        mma(a1, b1);
     }
     wait_vmcnt<0>();
     // nothing of the epilogue is scheduled into the last k-steps, where both fragment sets and all accumulators are live
     __builtin_amdgcn_sched_barrier(0);
-    prefill_epilogue_all<EPI, RM, RN>(p, rb * (A_FR / NP) + wm * RM, cb * B_FR + wn * RN, n_tiles, lane, acc);
+    prefill_epilogue_all<EPI, RM, RN>(p, rb * (WM * RM) + wm * RM, cb * B_FR + wn * RN, n_tiles, lane, acc);
 }
 // ---- weights of one layer as fp16 ------------------------------------------------------------------------------------
 // Element-wise bf16 -> fp16 of up to six packed matrices (fragment order is kept: the copy is read exactly like the
