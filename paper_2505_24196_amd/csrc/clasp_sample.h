@@ -103,8 +103,27 @@ struct AcceptShared {
     int reject[kMaxRows];
 };
 
+// Rows of at most kSmallVocab entries (the small models): a wavefront takes a row, so one workgroup, and one launch
+// // instead of three, does all of a call: 2064 entries, one draft 15 us with three launches of chunks and with the former workgroup
+// per call, 14 us now; seven drafts 31 us with that workgroup, 17 over chunks, 14 now (12 us of it the caller).
+constexpr int kSmallVocab = 4096;
+__device__ __forceinline__ RowStat small_row_stat(const float* lg, int V, float inv_t) {
+    const int lane = threadIdx.x & 63;
+    float m = -INFINITY, s = 0.f;
+#pragma unroll 8
+    for (int v = lane; v < V; v += 64) m = fmaxf(m, lg[v]);
+    m = wave_max(m);
+#pragma unroll 8
+    for (int v = lane; v < V; v += 64) {
+        const float x = lg[v];
+        s += x == -INFINITY ? 0.f : expf((x - m) * inv_t);
+    }
+    return RowStat{m, wave_sum(s)};
+}
+
 // The first rejected draft (n if none), by a whole workgroup; sh.row holds every row's (max, sum) afterwards. Draft i is
-// kept when u_accept[i] * q_i(x) < p_i(x).
+// kept when u_accept[i] * q_i(x) < p_i(x). SMALL: the rows' (max, sum) from the rows themselves, else from their chunks.
+template <bool SMALL>
 __device__ __forceinline__ int accept_prefix(const SampleArgs& a, int chunks, AcceptShared& sh) {
     const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6, i = threadIdx.x;
     float pl = 0.f, ql = 0.f, u = 0.f;  // this draft's logits and uniform number, requested beside the rows' pieces
@@ -115,7 +134,9 @@ __device__ __forceinline__ int accept_prefix(const SampleArgs& a, int chunks, Ac
         u = a.u_accept[i];
     }
     for (int r = wave; r < 2 * a.n + 1; r += nw) {
-        const RowStat st = merge_row(a.stats + (size_t)r * kSampleChunks, chunks, a.inv_t);
+        RowStat st;
+        if constexpr (SMALL) st = small_row_stat(r <= a.n ? a.p + (size_t)r * a.ld : a.q + (size_t)(r - a.n - 1) * a.ld, a.V, a.inv_t);
+        else st = merge_row(a.stats + (size_t)r * kSampleChunks, chunks, a.inv_t);
         if ((threadIdx.x & 63) == 0) sh.row[r] = st;
     }
     __syncthreads();
@@ -151,7 +172,7 @@ __global__ __launch_bounds__(kDrawThreads) void residual_sums_kernel(SampleArgs 
     __shared__ float red[kDrawThreads / 64];
     const SampleCut cut = sample_cut(a.V);
     const int lo = blockIdx.x * cut.size, hi = min(lo + cut.size, a.V);
-    const int first = accept_prefix(a, cut.chunks, sh);
+    const int first = accept_prefix<false>(a, cut.chunks, sh);
     if (first == a.n) return;
     const ResidualWeight w(a, first, sh);
     float s = 0.f;
@@ -245,26 +266,42 @@ __device__ __forceinline__ int draw_from_chunks(WF w, float total, const SampleC
 
 // One workgroup. Plain draw (q null): token ~ softmax(p / T). Acceptance: the replacement of the first rejected draft from
 // its residual, or from the full model's row where the residual is empty; the bonus token from row n when all are kept.
+// SMALL: the whole call for rows of at most kSmallVocab entries, which are one chunk.
+template <bool SMALL>
 __global__ __launch_bounds__(kDrawThreads) void draw_kernel(SampleArgs a) {
     __shared__ AcceptShared ac;
     __shared__ DrawShared sh;
-    const SampleCut cut = sample_cut(a.V);
+    __shared__ float red[kDrawThreads / 64];
+    const SampleCut cut = SMALL ? SampleCut{1, a.V} : sample_cut(a.V);
     const int lane = threadIdx.x & 63;
     const float u = a.u_final[0];
     int row = 0, tok = -1;
     RowStat ps;
     if (a.q) {
-        const float mass = lane < cut.chunks ? a.residual[lane] : 0.f;  // unwritten, and not used, when all drafts are kept
-        row = accept_prefix(a, cut.chunks, ac);
+        float mass = 0.f;  // unwritten, and not used, when all drafts are kept
+        if (!SMALL && lane < cut.chunks) mass = a.residual[lane];
+        row = accept_prefix<SMALL>(a, cut.chunks, ac);
         ps = ac.row[row];
-        if (row < a.n) tok = draw_from_chunks(ResidualWeight(a, row, ac), mass, cut, a.V, u, sh);
+        if (row < a.n) {
+            const ResidualWeight w(a, row, ac);
+            if constexpr (SMALL) {
+#pragma unroll 4
+                for (int v = threadIdx.x; v < a.V; v += kDrawThreads) mass += w(v);
+                mass = block_sum(mass, red);
+            }
+            tok = draw_from_chunks(w, mass, cut, a.V, u, sh);
+        }
     } else {
-        ps = merge_row(a.stats, cut.chunks, a.inv_t);
+        ps = SMALL ? small_row_stat(a.p, a.V, a.inv_t) : merge_row(a.stats, cut.chunks, a.inv_t);
     }
     if (tok < 0) {
         const float* p = a.p + (size_t)row * a.ld;
-        const RowStat st = lane < cut.chunks ? a.stats[(size_t)row * kSampleChunks + lane] : RowStat{-INFINITY, 0.f};
-        tok = draw_from_chunks([&](int v) { return expf((p[v] - ps.m) * a.inv_t); }, rescaled(st, ps.m, a.inv_t), cut, a.V, u, sh);
+        float total = ps.s;
+        if constexpr (!SMALL) {
+            const RowStat st = lane < cut.chunks ? a.stats[(size_t)row * kSampleChunks + lane] : RowStat{-INFINITY, 0.f};
+            total = rescaled(st, ps.m, a.inv_t);
+        }
+        tok = draw_from_chunks([&](int v) { return expf((p[v] - ps.m) * a.inv_t); }, total, cut, a.V, u, sh);
     }
     if (threadIdx.x == 0) {  // outputs last: every input of the call has been read by now
         if (a.q) a.n_accepted_out[0] = row;
