@@ -387,6 +387,18 @@ int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kin
             }
             return launch_gemv<EPI, KWV>(timer, g, gemv_lds, st);
         } else {
+            if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead) {
+                // Few enough column tiles for a workgroup each (the small models): eight wavefronts split K, so that a
+                // short contraction costs one trip to memory. K = 512, 176 tiles, 7 rows: 10.4 us with four tiles
+                // per wavefront and two K slices (22 workgroups, four trips), 6.1 us. With more tiles than CUs those
+                // wider workgroups win: their wavefronts share the activation loads.
+                if (tiles <= ctx->n_cu) {
+                    if (g.R == 1) launch_timed(timer, gemm_bf16_kernel<1, 1, 8, EPI, CLASP_STREAM_DEPTH, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
+                    else launch_timed(timer, gemm_bf16_kernel<2, 1, 8, EPI, 4, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
+                    CLASP_LAUNCH_CHECK();
+                    return CLASP_OK;
+                }
+            }
             if constexpr (EPI == kEpiQkv && NACC == 1 && CLASP_QKV_WIDE_NACC > 1) {
                 // a projection with at least two column tiles per CU and wavefront-to-be (the 70B shape's q|k|v: 640
                 // tiles) lets a wavefront carry several tiles, which share its activation loads, and still fills the chip
@@ -658,7 +670,8 @@ int run_head(const clasp_ctx* ctx, int n, int R, float* logits_out, int32_t* arg
         g.head_parts = static_cast<f32x4*>(ctx->head_parts);
         if ((rc = launch_gemm<kEpiHead, CLASP_HEAD_CW, CLASP_HEAD_KW>(ctx, g, st, CLASP_KERNEL_LM_HEAD))) return rc;
         if (want_head) {
-            hipLaunchKernelGGL(head_reduce_kernel, dim3(n), dim3(1024), 0, st, static_cast<const f32x4*>(ctx->head_parts),
+            const int threads = std::min(1024, (c.vocab / 16 + 63) / 64 * 64);  // at least a tile per thread
+            hipLaunchKernelGGL(head_reduce_kernel, dim3(n), dim3(threads), 0, st, static_cast<const f32x4*>(ctx->head_parts),
                                c.vocab / 16, argmax_out, margin_out, prob_out);
             CLASP_LAUNCH_CHECK();
         }

@@ -104,8 +104,8 @@ struct AcceptShared {
 };
 
 // Rows of at most kSmallVocab entries (the small models): a wavefront takes a row, so one workgroup, and one launch
-// // instead of three, does all of a call: 2064 entries, one draft 15 us with three launches of chunks and with the former workgroup
-// per call, 14 us now; seven drafts 31 us with that workgroup, 17 over chunks, 14 now (12 us of it the caller).
+// instead of three, does all of a call. 2064 entries, one draft: 15 us with a workgroup per call that walked the rows one
+// after another, 17 over chunks, 14 now; seven drafts: 31, 17, 14 (about 12 us of each is the caller).
 constexpr int kSmallVocab = 4096;
 __device__ __forceinline__ RowStat small_row_stat(const float* lg, int V, float inv_t) {
     const int lane = threadIdx.x & 63;

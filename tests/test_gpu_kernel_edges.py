@@ -183,3 +183,31 @@ def test_prompt_passes_at_the_edges_of_their_tiles(kind, d, heads, kv, hd, ffn):
                 assert err <= 2e-2, (kind, n, l, err)
     ref.close()
     eng.close()
+
+
+# The greedy head over tile counts at the edges of its threads and wavefronts (1, 63, 64, 65, 1024 and 1025 tiles, and more than
+# the 8 x 1024 of one round), with gate/up and lm_head on both sides of one workgroup per CU (256 tiles), one and two row
+# groups, and a contraction shorter and longer than the wavefronts' first stage. Rows of the row-limited path against the
+# oracle; argmax, margin and top-1 probability against the call's own logits (the margin exactly: the same fp32 numbers).
+@pytest.mark.parametrize("vocab,d,ffn", [(16, 64, 32), (1008, 64, 2048), (1024, 96, 2080), (1040, 512, 64), (4096, 64, 64),
+                                         (4112, 1056, 96), (16384, 64, 64), (16400, 64, 64), (131088, 64, 64)])
+def test_greedy_head_and_small_projections(vocab, d, ffn):
+    shape = si.ModelShape("edge-head", 2, d, 2, 1, 64, ffn, vocab, "bf16")
+    if vocab <= 4112:
+        verify_against_oracle(shape, (1, 3, 9, 16, 17, 32), 2e-2)
+    import paper_2505_24196_amd as clasp
+    eng = clasp.Engine(shape, max_seq=64, max_rows=32).load(si.gen_model(shape, 3, "cuda"))
+    for n in (1, 8, 9, 17):
+        toks = si.gen_tokens(5, n, vocab).cuda()
+        out = eng.clasp_verify_forward(toks, 0, want_logits=True, want_margin=True)
+        lg = out["logits"].double()
+        top = lg.topk(2, dim=1).values
+        assert torch.equal(out["argmax"].long(), lg.argmax(1))
+        assert torch.equal(out["margin"].double(), (out["logits"].topk(2, dim=1).values[:, 0] - top[:, 1].float()).double())
+    nxt, prob, q = torch.zeros(2, dtype=torch.int32, device="cuda"), torch.zeros(1, device="cuda"), torch.zeros(vocab, device="cuda")
+    eng.clasp_draft_step(None, toks[:1], 0, nxt[:1], prob)
+    eng.clasp_draft_sample(None, toks[:1], 0, 1.0, torch.zeros(1, device="cuda"), q, nxt[1:])
+    assert int(nxt[0]) == int(q.argmax())
+    want = torch.softmax(q.double(), 0).max().item()
+    assert abs(float(prob) / want - 1) <= 1e-5  # one rescaling and a tree of sums: about 20 roundings of 6e-8
+    eng.close()
