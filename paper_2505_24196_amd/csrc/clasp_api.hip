@@ -320,11 +320,7 @@ void launch_timed(const TimerScope& t, K kernel, dim3 grid, dim3 block, size_t l
 }
 
 // ---- GEMM dispatch ---------------------------------------------------------------------------------------------
-// Which projections may use the resident-activation kernel (bit = CLASP_KERNEL_* kind) when it applies (one row group
-// and K <= 32 * kResidentKW * kResidentKSW).
-#ifndef CLASP_RESIDENT_MASK
-#define CLASP_RESIDENT_MASK ((1 << CLASP_KERNEL_GATE_UP) | (1 << CLASP_KERNEL_LM_HEAD))
-#endif
+// Resident-activation kernels: K slices (wavefronts) and k-steps a slice may have.
 constexpr int kResidentKW = 8, kResidentKSW = 16;
 
 constexpr size_t kGemvMaxLds = 96 * 1024;
@@ -353,80 +349,98 @@ int launch_gemv(const TimerScope& timer, const GemmArgs& g, size_t lds, hipStrea
     return CLASP_OK;
 }
 
-template <int EPI, int CW, int KW, int NACC = 1, int R2NACC = CLASP_R2_NACC, int R2CW = CW, int R2KW = KW>
-int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kind) {
+// 1..CLASP_FEW_ROWS rows of gate|up or lm_head: the rows sit in LDS, the registers hold a whole tile slice of weights per
+// wavefront.
+template <int EPI>
+int launch_few_rows(const clasp_ctx* ctx, const TimerScope& timer, const GemmArgs& g, hipStream_t st) {
+    auto kernel = gemv_persistent_bf16_kernel<kResidentKSW, kResidentKW, EPI, CLASP_GEMVP_DEPTH, CLASP_ACT_SPLIT>;
+    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
+    if (!opted_in) {
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * kFewRows) != hipSuccess)
+            return CLASP_E_HIP;
+        opted_in = true;
+    }
+    const int tiles = g.N / 16, rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
+    launch_timed(timer, kernel, dim3(grid), dim3((kResidentKW + 1) * 64),
+                 (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * g.n_rows, st, g);
+    CLASP_LAUNCH_CHECK();
+    return CLASP_OK;
+}
+
+template <int EPI, int CW, int KW, int NACC, int R2NACC, int R2CW, int R2KW>
+int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmArgs& g, hipStream_t st, int kind) {
     const int tiles = g.N / 16;
-    TimerScope timer(ctx, kind, st, false);
-    if (ctx->cfg.dtype == CLASP_BF16) {
-        const bool resident = g.R == 1 && ((CLASP_RESIDENT_MASK >> kind) & 1) &&
-                              (g.K / 32 + kResidentKW - 1) / kResidentKW <= kResidentKSW && tiles > ctx->n_cu;
-        constexpr int KWV = EPI == kEpiQkv ? CLASP_GEMV_KW_QKV : (EPI == kEpiResid ? CLASP_GEMV_KW_RESID : 8);
-        const size_t gemv_lds =
-            (CLASP_GEMV && g.n_rows == 1 && g.R == 1 && EPI != kEpiPartial) ? gemv_lds_bytes<KWV>(g.K) : 0;
-        if (resident && CLASP_GEMV_PERSISTENT && g.n_rows <= CLASP_FEW_ROWS) {
-            // few rows: they sit in LDS, the registers hold a whole tile slice of weights per wavefront
-            auto kernel = gemv_persistent_bf16_kernel<kResidentKSW, kResidentKW, EPI, CLASP_GEMVP_DEPTH, CLASP_ACT_SPLIT>;
-            static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-            if (!opted_in) {
-                if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * kFewRows) != hipSuccess)
-                    return CLASP_E_HIP;
-                opted_in = true;
-            }
-            const int rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
-            launch_timed(timer, kernel, dim3(grid), dim3((kResidentKW + 1) * 64),
-                         (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * g.n_rows, st, g);
-        } else if (resident && !(gemv_lds && kind == CLASP_KERNEL_LM_HEAD)) {  // one-row lm_head: the single-row kernel is 3 % faster
-            // every workgroup takes the same number of tiles (+-1): rounds = ceil(tiles / CUs), grid = ceil(tiles / rounds)
-            const int rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
+    // gate|up and lm_head on one row group, K short enough for its rows to stay on the CU, more tiles than CUs
+    const bool resident = (EPI == kEpiSwiglu || EPI == kEpiHead) && g.R == 1 &&
+                          (g.K / 32 + kResidentKW - 1) / kResidentKW <= kResidentKSW && tiles > ctx->n_cu;
+    if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead) {
+        if (resident && CLASP_GEMV_PERSISTENT && g.n_rows <= CLASP_FEW_ROWS) return launch_few_rows<EPI>(ctx, timer, g, st);
+    }
+    constexpr int KWV = EPI == kEpiQkv ? CLASP_GEMV_KW_QKV : (EPI == kEpiResid ? CLASP_GEMV_KW_RESID : 8);
+    const size_t gemv_lds =
+        (CLASP_GEMV && g.n_rows == 1 && g.R == 1 && EPI != kEpiPartial) ? gemv_lds_bytes<KWV>(g.K) : 0;
+    if (resident && !(gemv_lds && kind == CLASP_KERNEL_LM_HEAD)) {  // one-row lm_head: the single-row kernel is 3 % faster
+        // every workgroup takes the same number of tiles (+-1): rounds = ceil(tiles / CUs), grid = ceil(tiles / rounds)
+        const int rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
+        if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead)
             launch_timed(timer, gemm_bf16_resident_kernel<kResidentKSW, kResidentKW, EPI, CLASP_GEMM_DEPTH, CLASP_ACT_SPLIT>,
                          dim3(grid), dim3(kResidentKW * 64), 0, st, g);
-        } else if (gemv_lds) {
-            if constexpr (EPI == kEpiResid) {
-                if (g.attn_partial) return launch_gemv<EPI, KWV, 1>(timer, g, gemv_lds, st);
-            }
-            return launch_gemv<EPI, KWV>(timer, g, gemv_lds, st);
-        } else {
-            if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead) {
-                // Few enough column tiles for a workgroup each (the small models): eight wavefronts split K, so that a
-                // short contraction costs one trip to memory. K = 512, 176 tiles, 7 rows: 10.4 us with four tiles
-                // per wavefront and two K slices (22 workgroups, four trips), 6.1 us. With more tiles than CUs those
-                // wider workgroups win: their wavefronts share the activation loads.
-                if (tiles <= ctx->n_cu) {
-                    if (g.R == 1) launch_timed(timer, gemm_bf16_kernel<1, 1, 8, EPI, CLASP_STREAM_DEPTH, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
-                    else launch_timed(timer, gemm_bf16_kernel<2, 1, 8, EPI, 4, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
-                    CLASP_LAUNCH_CHECK();
-                    return CLASP_OK;
-                }
-            }
-            if constexpr (EPI == kEpiQkv && NACC == 1 && CLASP_QKV_WIDE_NACC > 1) {
-                // a projection with at least two column tiles per CU and wavefront-to-be (the 70B shape's q|k|v: 640
-                // tiles) lets a wavefront carry several tiles, which share its activation loads, and still fills the chip
-                if (g.R == 1 && tiles >= 2 * ctx->n_cu) {
-                    constexpr int WN = CLASP_QKV_WIDE_NACC;
-                    launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / WN, CLASP_ACT_SPLIT, WN>,
-                                 dim3((tiles + CW * WN - 1) / (CW * WN)), dim3(CW * KW * 64), 0, st, g);
-                    CLASP_LAUNCH_CHECK();
-                    return CLASP_OK;
-                }
-            }
-            if (g.R == 1) {  // NACC tiles per wavefront share the activation fragments; the stage depth shrinks to match
-                const dim3 grid((tiles + CW * NACC - 1) / (CW * NACC));
-                launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / NACC, CLASP_ACT_SPLIT, NACC>, grid,
-                             dim3(CW * KW * 64), 0, st, g);
-            } else {
-                // two row groups: R2NACC column tiles per wavefront share the four activation loads of a k-step (weight
-                // fragments per stage stay the same, so fewer tiles per wavefront mean more k-steps per stage)
-                const dim3 grid((tiles + R2CW * R2NACC - 1) / (R2CW * R2NACC));
-                launch_timed(timer, gemm_bf16_kernel<2, R2CW, R2KW, EPI, CLASP_R2_DEPTH * CLASP_R2_NACC / R2NACC, CLASP_ACT_SPLIT, R2NACC>,
-                             grid, dim3(R2CW * R2KW * 64), 0, st, g);
+    } else if (gemv_lds) {
+        if constexpr (EPI == kEpiResid) {
+            if (g.attn_partial) return launch_gemv<EPI, KWV, 1>(timer, g, gemv_lds, st);
+        }
+        return launch_gemv<EPI, KWV>(timer, g, gemv_lds, st);
+    } else {
+        if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead) {
+            // Few enough column tiles for a workgroup each (the small models): eight wavefronts split K, so that a
+            // short contraction costs one trip to memory. K = 512, 176 tiles, 7 rows: 10.4 us with four tiles
+            // per wavefront and two K slices (22 workgroups, four trips), 6.1 us. With more tiles than CUs those
+            // wider workgroups win: their wavefronts share the activation loads.
+            if (tiles <= ctx->n_cu) {
+                if (g.R == 1) launch_timed(timer, gemm_bf16_kernel<1, 1, 8, EPI, CLASP_STREAM_DEPTH, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
+                else launch_timed(timer, gemm_bf16_kernel<2, 1, 8, EPI, 4, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
+                CLASP_LAUNCH_CHECK();
+                return CLASP_OK;
             }
         }
-    } else {
-        if constexpr (EPI == kEpiQkv || EPI == kEpiHead || EPI == kEpiPartial) return CLASP_E_UNSUPPORTED;
-        else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(tiles), dim3(512), 0, st, g);
-        else launch_timed(timer, gemm_f32_kernel<EPI, 2>, dim3(tiles), dim3(512), 0, st, g);
+        if constexpr (EPI == kEpiQkv && NACC == 1 && CLASP_QKV_WIDE_NACC > 1) {
+            // a projection with at least two column tiles per CU and wavefront-to-be (the 70B shape's q|k|v: 640
+            // tiles) lets a wavefront carry several tiles, which share its activation loads, and still fills the chip
+            if (g.R == 1 && tiles >= 2 * ctx->n_cu) {
+                constexpr int WN = CLASP_QKV_WIDE_NACC;
+                launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / WN, CLASP_ACT_SPLIT, WN>,
+                             dim3((tiles + CW * WN - 1) / (CW * WN)), dim3(CW * KW * 64), 0, st, g);
+                CLASP_LAUNCH_CHECK();
+                return CLASP_OK;
+            }
+        }
+        if (g.R == 1) {  // NACC tiles per wavefront share the activation fragments; the stage depth shrinks to match
+            const dim3 grid((tiles + CW * NACC - 1) / (CW * NACC));
+            launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / NACC, CLASP_ACT_SPLIT, NACC>, grid,
+                         dim3(CW * KW * 64), 0, st, g);
+        } else {
+            // two row groups: R2NACC column tiles per wavefront share the four activation loads of a k-step (weight
+            // fragments per stage stay the same, so fewer tiles per wavefront mean more k-steps per stage)
+            const dim3 grid((tiles + R2CW * R2NACC - 1) / (R2CW * R2NACC));
+            launch_timed(timer, gemm_bf16_kernel<2, R2CW, R2KW, EPI, CLASP_R2_DEPTH * CLASP_R2_NACC / R2NACC, CLASP_ACT_SPLIT, R2NACC>,
+                         grid, dim3(R2CW * R2KW * 64), 0, st, g);
+        }
     }
+    CLASP_LAUNCH_CHECK();
+    return CLASP_OK;
+}
+
+template <int EPI, int CW, int KW, int NACC = 1, int R2NACC = CLASP_R2_NACC, int R2CW = CW, int R2KW = KW>
+int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kind) {
+    TimerScope timer(ctx, kind, st, false);
+    if (ctx->cfg.dtype == CLASP_BF16) {
+        if constexpr (EPI == kEpiScale) return CLASP_E_UNSUPPORTED;  // fp32 models only
+        else return launch_gemm_bf16<EPI, CW, KW, NACC, R2NACC, R2CW, R2KW>(ctx, timer, g, st, kind);
+    }
+    if constexpr (EPI == kEpiQkv || EPI == kEpiHead || EPI == kEpiPartial) return CLASP_E_UNSUPPORTED;  // bf16 models only
+    else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(g.N / 16), dim3(512), 0, st, g);
+    else launch_timed(timer, gemm_f32_kernel<EPI, 2>, dim3(g.N / 16), dim3(512), 0, st, g);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }

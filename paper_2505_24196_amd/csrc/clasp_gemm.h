@@ -11,7 +11,7 @@
 //
 // Epilogues (they produce what the NEXT kernel consumes, so that no separate norm / rotary / activation kernels
 // exist):
-//   kEpiScale   out = acc * rstd(row)                       (lm_head; fp32 path q/k/v; RMSNorm's 1/rms factor
+//   kEpiScale   out = acc * rstd(row)                       (fp32 path: q/k/v and lm_head; RMSNorm's 1/rms factor
 //                                                            commutes with the contraction, its gains are already
 //                                                            folded into the activation fragments)
 //   kEpiResid   out = resid + acc; optionally a copy (hidden-state capture), the next GEMM's operand
@@ -175,10 +175,9 @@ __device__ __forceinline__ void gemm_issue(GemmStage<R, NACC, P, SPLIT>& st, con
     }
 }
 
-// WT = false: accumulator tile D[row][feature], a lane holds rows 4*(lane/16) .. +3 of feature lane%16.
-// WT = true (weights as the first operand): D[feature][row], a lane holds features 4*(lane/16) .. +3 of row lane%16,
-// i.e. four consecutive columns of one output row: what the epilogues that write rows (residual, K-slices) want.
-template <int R, int NACC, int P, int SPLIT, bool WT = false>
+// Weights are the first operand: accumulator tile D[feature][row], a lane holds features 4*(lane/16) .. +3 of row lane%16,
+// i.e. four consecutive columns of one output row, which is what the epilogues want.
+template <int R, int NACC, int P, int SPLIT>
 __device__ __forceinline__ void gemm_compute(const GemmStage<R, NACC, P, SPLIT>& st, f32x4 (&acc)[NACC][R], int s,
                                              int ks1) {
 #pragma unroll
@@ -189,169 +188,22 @@ __device__ __forceinline__ void gemm_compute(const GemmStage<R, NACC, P, SPLIT>&
 #pragma unroll
                 for (int h = 0; h < SPLIT; ++h)
 #pragma unroll
-                    for (int a = 0; a < NACC; ++a) {
-                        if constexpr (WT)
-                            acc[a][rg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.b[a][u]),
-                                                                                 as_bf16x8(st.a[u][rg][h]), acc[a][rg], 0, 0, 0);
-                        else
-                            acc[a][rg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.a[u][rg][h]),
-                                                                                 as_bf16x8(st.b[a][u]), acc[a][rg], 0, 0, 0);
-                    }
+                    for (int a = 0; a < NACC; ++a)
+                        acc[a][rg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(st.b[a][u]), as_bf16x8(st.a[u][rg][h]),
+                                                                             acc[a][rg], 0, 0, 0);
         }
     }
 }
 
-// Inputs of the epilogue that do not depend on the contraction (residual values, gain, rotary factors). The
-// epilogue wavefront requests them before the main loop so that the tail of the kernel has no dependent global load.
-struct EpiPre {
-    float resid[4];
-    float2 cs[4];
-    float gain;
-};
-
-template <int EPI>
-__device__ __forceinline__ void epi_prefetch(const GemmArgs& g, int tile, int lane, int rg, EpiPre& pre) {
-    const int c = lane & 15, col = tile * 16 + c, row0 = rg * 16 + (lane >> 4) * 4;
-    if constexpr (EPI == kEpiResid) {
-        pre.gain = g.next_gain ? g.next_gain[col] : 1.0f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) pre.resid[r] = (row0 + r < g.n_rows) ? g.resid[(size_t)(row0 + r) * g.ldr + col] : 0.f;
-    } else if constexpr (EPI == kEpiQkv) {
-        const QkvOut& o = g.qkv;
-        const int HALF = o.head_dim >> 1, tph = o.head_dim >> 4;
-        const int tl = tile - (tile < g.tile_end[0] ? 0 : g.tile_end[0]);  // q or k tile inside its matrix
-        const int e = (tl % tph) * 8 + (c & 7);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            pre.cs[r] = (tile < g.tile_end[1] && row < g.n_rows) ? o.rope[(size_t)(o.pos0 + (o.mode ? row : 0)) * HALF + e]
-                                                                  : make_float2(1.f, 0.f);
-        }
-    }
-}
-
-// q/k/v epilogue of one lane: 4 rows x 1 feature of tile `tile` (see kEpiQkv above).
-__device__ __forceinline__ void qkv_epilogue(const GemmArgs& g, int tile, int lane, int rg, const f32x4& sum,
-                                             const float* rstd_s, const EpiPre& pre) {
-    const QkvOut& o = g.qkv;
-    const int HD = o.head_dim, HALF = HD >> 1, tph = HD >> 4;  // tiles per head
-    const int c = lane & 15, row0 = rg * 16 + (lane >> 4) * 4;
-    const int G = o.n_heads / o.n_kv_heads;
-    const int which = tile < g.tile_end[0] ? 0 : (tile < g.tile_end[1] ? 1 : 2);
-    const int tl = tile - (which == 0 ? 0 : g.tile_end[which - 1]);
-    const int head = tl / tph, u = tl % tph;
-    kv_t* kc = reinterpret_cast<kv_t*>(o.k_cache);
-    kv_t* vc = reinterpret_cast<kv_t*>(o.v_cache);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int row = row0 + r;
-        const float own = sum[r] * rstd_s[row & 31];
-        const float partner = __shfl_xor(own, 8);
-        if (which == 2) {  // v: plain feature order
-            const int x = u * 16 + c;
-            if (row < g.n_rows) {
-                const kv_t v = to_kv(own);
-                if (o.mode) vc[(size_t)head * o.t_max * HD + vfrag_offset(HD, o.pos0 + row, x)] = v;
-                else reinterpret_cast<kv_t*>(o.v_self)[(size_t)head * 32 * HD + vfrag_offset(HD, row, x)] = v;
-            }
-            continue;
-        }
-        // q / k: lanes 0..7 hold feature e = 8u + c, lanes 8..15 its rotary partner e + HALF
-        const int e = u * 8 + (c & 7), x = e + ((c & 8) ? HALF : 0);
-        if (row < g.n_rows) {
-            const int pos = o.pos0 + (o.mode ? row : 0);
-            const float2 cs = pre.cs[r];
-            const float rot = own * cs.x + ((c & 8) ? partner : -partner) * cs.y;
-            if (which == 0) {
-                const int kvh = head / G, qi = row * G + head % G;
-                const size_t off = (((((size_t)kvh * (2 * G) + (qi >> 4)) * (HD >> 5) + (x >> 5)) * 64) +
-                                    ((x >> 3) & 3) * 16 + (qi & 15)) * 8 + (x & 7);
-                reinterpret_cast<kv_t*>(o.q_frag)[off] = to_kv(rot * o.q_scale);
-            } else if (o.mode) {
-                kc[(size_t)head * o.t_max * HD + kfrag_offset(HD, pos, x)] = to_kv(rot);
-            } else {
-                reinterpret_cast<kv_t*>(o.k_self)[(size_t)head * 32 * HD + kfrag_offset(HD, row, x)] = to_kv(rot);
-            }
-        }
-    }
-}
-
-// Epilogue of one (tile, row group) for one lane: 4 rows x 1 feature; sum[a] = finished accumulators.
-template <int EPI, int NACC>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, int tile, int lane, int rg, const f32x4 (&sum)[NACC],
-                                              const float* rstd_s, const EpiPre& pre) {
-    const int col = tile * 16 + (lane & 15);
-    const int row0 = rg * 16 + (lane >> 4) * 4;
-    if constexpr (EPI == kEpiScale) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            if (row < g.n_rows) g.out[(size_t)row * g.ldo + col] = sum[0][r] * rstd_s[row];
-        }
-    } else if constexpr (EPI == kEpiQkv) {
-        qkv_epilogue(g, tile, lane, rg, sum[0], rstd_s, pre);
-    } else if constexpr (EPI == kEpiHead) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            if (row >= g.n_rows) continue;  // uniform over the 16 lanes that share a row; the shuffles stay inside them
-            const float x = sum[0][r] * rstd_s[row];
-            if (g.out) g.out[(size_t)row * g.ldo + col] = x;
-            float v1 = x, v2 = -INFINITY;
-            int i1 = col;
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                const float b1 = __shfl_xor(v1, o), b2 = __shfl_xor(v2, o);
-                const int bi = __shfl_xor(i1, o);
-                top2_merge(v1, i1, v2, b1, bi, b2);
-            }
-            const float se = sum16(expf(x - v1));
-            if ((lane & 15) == 0) g.head_parts[(size_t)row * (g.N >> 4) + tile] = f32x4{v1, __int_as_float(i1), v2, se};
-        }
-    } else if constexpr (EPI == kEpiPartial) {
-        float* slab = g.out + (size_t)blockIdx.y * g.ldr;  // ldr = elements per slab
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            if (row < g.n_rows) slab[(size_t)row * g.ldo + col] = sum[0][r];
-        }
-    } else if constexpr (EPI == kEpiResid) {
-        const float gain = pre.gain;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            float v = 0.f;
-            if (row < g.n_rows) {
-                v = pre.resid[r] + sum[0][r];
-                g.out[(size_t)row * g.ldo + col] = v;
-                if (g.capture) g.capture[(size_t)row * g.ldc + col] = v;
-            }
-            if (g.next_op) store_operand<kDtBf16>(g.next_op, g.R, 0, row, col, v * gain);
-            if (g.next_ss) {
-                const float sq = sum16(v * v);
-                if ((lane & 15) == 0) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
-            }
-        }
-    } else {
-        // the packed gate|up matrix interleaves the two projections: lanes 0..7 of a tile hold gate features
-        // 8*tile .. 8*tile+7, lanes 8..15 the matching up features
-        const int c = lane & 15;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = row0 + r;
-            const float own = sum[0][r] * rstd_s[row & 31];
-            const float up = __shfl_xor(own, 8);
-            const float v = (row < g.n_rows) ? own / (1.0f + expf(-own)) * up : 0.f;
-            if (c < 8) store_operand<kDtBf16>(g.next_op, g.R, 0, row, tile * 8 + c, v);
-        }
-    }
-}
-
-// The residual and K-slice epilogues on a transposed accumulator tile (gemm_compute<.., WT = true>): a lane owns columns
-// tile*16 + 4*(lane/16) .. +3 of row rg*16 + lane%16, so the residual, the output row, the captured state and the
-// next GEMM's operand move as 16-byte (operand planes: 8-byte) pieces, and a row's sum of squares over the tile needs
-// two shuffles. With one feature per lane the same epilogue took 12-16 stores of 2 or 4 bytes and 16 shuffles per lane
-// at the very end of the kernel, where nothing overlaps them.
+// The epilogues work on a transposed accumulator tile (weights as the MFMA's first operand): a lane owns features tile*16 +
+// 4*(lane/16) .. +3 of row rg*16 + lane%16, so the residual, the output row, the captured state, the logits and the next
+// GEMM's operand move as 16-byte (operand planes: 8-byte) pieces, and what is reduced over a row's tile (sum of squares,
+// the greedy head's largest logits) needs two shuffle steps. With one feature per lane the same epilogues took 12-16 stores
+// of 2 or 4 bytes and 16 shuffles (greedy head: 64) per lane at the very end of the kernel, where nothing overlaps them.
+// Rows that do not exist are not written: every reader clamps to the last live row.
+//
+// Inputs of the epilogue that do not depend on the contraction (residual values, gain, rotary factors). The epilogue
+// wavefront requests them before the main loop so that the tail of the kernel has no dependent global load.
 struct EpiPreT {
     f32x4 resid, gain;
     f32x4 cs[2];  // rotary (cos, sin) of the lane's four features
@@ -435,35 +287,65 @@ __device__ __forceinline__ void qkv_epilogue_t(const GemmArgs& g, int tile, int 
 template <int EPI>
 __device__ __forceinline__ void gemm_epilogue_t(const GemmArgs& g, int tile, int lane, int rg, const f32x4& sum,
                                                 const float* rstd_s, const EpiPreT& pre) {
-    static_assert(EPI == kEpiResid || EPI == kEpiPartial || EPI == kEpiQkv, "row-writing epilogues only");
     const int row = rg * 16 + (lane & 15), col0 = tile * 16 + (lane >> 4) * 4;
+    const bool live = row < g.n_rows;
+    auto store4 = [](float* base, int ld, int r, int col, const f32x4& v) {  // a caller's buffer may not be 16-byte aligned
+        float* p = base + (size_t)r * ld + col;
+        if ((reinterpret_cast<uintptr_t>(base) & 15) == 0 && (ld & 3) == 0) {
+            *reinterpret_cast<f32x4*>(p) = v;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = v[e];
+        }
+    };
     if constexpr (EPI == kEpiQkv) {
         qkv_epilogue_t(g, tile, lane, rg, sum, rstd_s, pre);
     } else if constexpr (EPI == kEpiPartial) {
         float* slab = g.out + (size_t)blockIdx.y * g.ldr;  // ldr = elements per slab
-        if (row < g.n_rows) *reinterpret_cast<f32x4*>(slab + (size_t)row * g.ldo + col0) = sum;
-    } else {
+        if (live) *reinterpret_cast<f32x4*>(slab + (size_t)row * g.ldo + col0) = sum;
+    } else if constexpr (EPI == kEpiResid) {
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (row < g.n_rows) {
+        if (live) {
             v = pre.resid + sum;
             *reinterpret_cast<f32x4*>(g.out + (size_t)row * g.ldo + col0) = v;
-            if (g.capture) {  // the caller's buffer: 16-byte stores only if it is aligned for them
-                float* cp = g.capture + (size_t)row * g.ldc + col0;
-                if ((reinterpret_cast<uintptr_t>(g.capture) & 15) == 0 && (g.ldc & 3) == 0) {
-                    *reinterpret_cast<f32x4*>(cp) = v;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) cp[e] = v[e];
-                }
-            }
+            if (g.capture) store4(g.capture, g.ldc, row, col0, v);
+            if (g.next_op) store_operand4<kDtBf16>(g.next_op, g.R, 0, row, col0, v * pre.gain);
         }
-        if (g.next_op) store_operand4<kDtBf16>(g.next_op, g.R, 0, row, col0, v * pre.gain);
         if (g.next_ss) {
             float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
             sq += __shfl_xor(sq, 16);
             sq += __shfl_xor(sq, 32);
-            if (lane < 16) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
+            if (live && lane < 16) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
         }
+    } else if constexpr (EPI == kEpiSwiglu) {
+        // the packed gate|up matrix interleaves the two projections: features 0..7 of a tile are gate features 8*tile ..
+        // 8*tile+7, features 8..15 (32 lanes on) the matching up features
+        const float rs = rstd_s[row];
+        f32x4 v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float own = sum[i] * rs, up = __shfl_xor(own, 32);
+            v[i] = own / (1.0f + expf(-own)) * up;
+        }
+        if (live && lane < 32) store_operand4<kDtBf16>(g.next_op, g.R, 0, row, tile * 8 + (lane >> 4) * 4, v);
+    } else {
+        static_assert(EPI == kEpiHead, "bf16 epilogues");
+        const f32x4 x = sum * rstd_s[row];
+        if (g.out && live) store4(g.out, g.ldo, row, col0, x);
+        float v1 = x[0], v2 = -INFINITY;
+        int i1 = col0;
+#pragma unroll
+        for (int i = 1; i < 4; ++i) top2_merge(v1, i1, v2, x[i], col0 + i, -INFINITY);
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1) {
+            const float b1 = __shfl_xor(v1, o), b2 = __shfl_xor(v2, o);
+            const int bi = __shfl_xor(i1, o);
+            top2_merge(v1, i1, v2, b1, bi, b2);
+        }
+        float se = (expf(x[0] - v1) + expf(x[1] - v1)) + (expf(x[2] - v1) + expf(x[3] - v1));
+        se += __shfl_xor(se, 16);
+        se += __shfl_xor(se, 32);
+        if (live && lane < 16) g.head_parts[(size_t)row * (g.N >> 4) + tile] = f32x4{v1, __int_as_float(i1), v2, se};
     }
 }
 
@@ -494,7 +376,7 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
     for (int a = 0; a < NACC; ++a) {
         tile[a] = min(tile0 + a, n_tiles - 1);  // tiles beyond the last shadow it, their result is dropped
         int mi = 0, tl = tile[a];
-        if constexpr (EPI == kEpiScale || EPI == kEpiQkv) {
+        if constexpr (EPI == kEpiQkv) {
             if (tile[a] >= g.tile_end[0]) { mi = 1; tl = tile[a] - g.tile_end[0]; }
             if (tile[a] >= g.tile_end[1]) { mi = 2; tl = tile[a] - g.tile_end[1]; }
         }
@@ -517,26 +399,22 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
     int s = ks0;
     if (s < ks1) gemm_issue<R, NACC, P, SPLIT>(st0, w, af, s, ks1);  // weights first: independent of rstd
 
-    constexpr bool kWT = (EPI == kEpiResid || EPI == kEpiPartial || EPI == kEpiQkv);  // row-writing epilogues take transposed tiles
-    typename std::conditional<kWT, EpiPreT, EpiPre>::type pre[NACC][R];
+    EpiPreT pre[NACC][R];
     if (kw == 0) {
 #pragma unroll
         for (int a = 0; a < NACC; ++a)
 #pragma unroll
-            for (int rg = 0; rg < R; ++rg) {
-                if constexpr (kWT) epi_prefetch_t<EPI>(g, tile[a], lane, rg, pre[a][rg]);
-                else epi_prefetch<EPI>(g, tile[a], lane, rg, pre[a][rg]);
-            }
+            for (int rg = 0; rg < R; ++rg) epi_prefetch_t<EPI>(g, tile[a], lane, rg, pre[a][rg]);
     }
     if constexpr (EPI != kEpiResid && EPI != kEpiPartial) compute_rstd(g, rstd_s, tmp_s);
 
     while (s < ks1) {
         if (s + P < ks1) gemm_issue<R, NACC, P, SPLIT>(st1, w, af, s + P, ks1);
-        gemm_compute<R, NACC, P, SPLIT, kWT>(st0, acc, s, ks1);
+        gemm_compute<R, NACC, P, SPLIT>(st0, acc, s, ks1);
         s += P;
         if (s >= ks1) break;
         if (s + P < ks1) gemm_issue<R, NACC, P, SPLIT>(st0, w, af, s + P, ks1);
-        gemm_compute<R, NACC, P, SPLIT, kWT>(st1, acc, s, ks1);
+        gemm_compute<R, NACC, P, SPLIT>(st1, acc, s, ks1);
         s += P;
     }
 
@@ -569,15 +447,7 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
     for (int a = 0; a < NACC; ++a) {
         if (tile0 + a >= n_tiles) continue;
 #pragma unroll
-        for (int rg = 0; rg < R; ++rg) {
-            if constexpr (kWT) {
-                gemm_epilogue_t<EPI>(g, tile[a], lane, rg, sum[a][rg], rstd_s, pre[a][rg]);
-            } else {
-                f32x4 fin[1];
-                fin[0] = sum[a][rg];
-                gemm_epilogue<EPI, 1>(g, tile[a], lane, rg, fin, rstd_s, pre[a][rg]);
-            }
-        }
+        for (int rg = 0; rg < R; ++rg) gemm_epilogue_t<EPI>(g, tile[a], lane, rg, sum[a][rg], rstd_s, pre[a][rg]);
     }
 }
 
@@ -605,7 +475,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
     const int ks0 = (KS * kw) / KW, ks1 = (KS * (kw + 1)) / KW, nks = ks1 - ks0;
 
     int mi = 0, tl = tile;
-    if constexpr (EPI == kEpiScale || EPI == kEpiQkv) {
+    if constexpr (EPI == kEpiQkv) {
         if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
         if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
     }
@@ -621,7 +491,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
     // piece e of the slice = (k-step e / (4*SPLIT), plane (e / 4) % SPLIT, 16-byte quarter e % 4) of row 0
     const int n_el = nks * SPLIT * 4;
     u32x4* mine = a_lds + (size_t)kw * nks_max * SPLIT * 4;
-    EpiPre pre;
+    EpiPreT pre;
     float ssv[16];
     if constexpr (ASRC == 0) {
         u32x4 av[kGemvLoads];
@@ -631,7 +501,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
             const int e = min(lane + i * 64, max(n_el - 1, 0));
             av[i] = A[((size_t)(ks0 + e / (4 * SPLIT)) * 2 + (e / 4) % SPLIT) * 64 + (e & 3)];
         }
-        if (kw == 0) epi_prefetch<EPI>(g, tile, lane, 0, pre);
+        if (kw == 0) epi_prefetch_t<EPI>(g, tile, lane, 0, pre);
         if constexpr (kNeedsRstd) rstd_issue(g, ssv);
         if (s + P < ks1) issue(wb[1], s + P);
 #pragma unroll
@@ -688,7 +558,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
         };
         Piece pc;
         if (lane < nks * 4) fetch(pc, lane);  // ahead of the second weight stage, like the operand loads above
-        if (kw == 0) epi_prefetch<EPI>(g, tile, lane, 0, pre);
+        if (kw == 0) epi_prefetch_t<EPI>(g, tile, lane, 0, pre);
         if (s + P < ks1) issue(wb[1], s + P);
         if (lane < nks * 4) merge_store(pc, lane);
         for (int pp = lane + 64; pp < nks * 4; pp += 64) {
@@ -709,8 +579,8 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
             if (s0 + u < ks1) {
 #pragma unroll
                 for (int h = 0; h < SPLIT; ++h)
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(mine[((s0 + u - ks0) * SPLIT + h) * 4 + q]),
-                                                                  as_bf16x8(buf[u]), acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(buf[u]),
+                                                                  as_bf16x8(mine[((s0 + u - ks0) * SPLIT + h) * 4 + q]), acc, 0, 0, 0);
             }
         }
     };
@@ -728,10 +598,9 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
     __syncthreads();
     if (kw != 0) return;
     if constexpr (kNeedsRstd) rstd_finish(g, tmp_s, rstd_s);
-    f32x4 fin[1];
-    fin[0] = red[0][lane];
-    for (int k = 1; k < KW; ++k) fin[0] += red[k][lane];
-    gemm_epilogue<EPI, 1>(g, tile, lane, 0, fin, rstd_s, pre);
+    f32x4 fin = red[0][lane];
+    for (int k = 1; k < KW; ++k) fin += red[k][lane];
+    gemm_epilogue_t<EPI>(g, tile, lane, 0, fin, rstd_s, pre);
 }
 
 // Few-row kernel (1..kFewRows rows) for projections with more column tiles than the GPU has CUs (gate|up, lm_head):
@@ -746,48 +615,35 @@ constexpr int kFewRows = 8;
 template <int KSW, int KW, int EPI, int P, int SPLIT>
 __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(GemmArgs g) {
     static_assert(KSW % P == 0, "a tile slice is a whole number of stages");
+    static_assert(EPI == kEpiSwiglu || EPI == kEpiHead, "one matrix, and both need the rows' 1/rms");
     constexpr int NST = KSW / P;
     extern __shared__ u32x4 a_s[];  // [KW][KSW * SPLIT * 4 * rows]
     __shared__ f32x4 red[2][KW][64];
     __shared__ float rstd_s[kMaxRows];
     __shared__ float tmp_s[(KW + 1) * 64];
-    constexpr bool kNeedsRstd = EPI != kEpiResid && EPI != kEpiPartial;
     const int kw = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
     const int n_tiles = g.N >> 4, KS = g.K >> 5;
     float ssv[16];
-    if constexpr (kNeedsRstd) rstd_issue(g, ssv);
+    rstd_issue(g, ssv);
 
     if (kw == KW) {  // the epilogue wavefront
-        if constexpr (kNeedsRstd) rstd_stash(g, ssv, tmp_s);
+        rstd_stash(g, ssv, tmp_s);
         int it = 0;
         for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x, ++it) {
-            EpiPre pre;
-            epi_prefetch<EPI>(g, tile, lane, 0, pre);
             __syncthreads();  // the KW partial tiles of `tile` are in red[it & 1]
-            if constexpr (kNeedsRstd) {
-                if (it == 0) rstd_finish(g, tmp_s, rstd_s);
-            }
+            if (it == 0) rstd_finish(g, tmp_s, rstd_s);
             f32x4(&rb)[KW][64] = red[it & 1];
-            f32x4 fin[1];
-            fin[0] = rb[0][lane];
-            for (int k = 1; k < KW; ++k) fin[0] += rb[k][lane];
-            gemm_epilogue<EPI, 1>(g, tile, lane, 0, fin, rstd_s, pre);
+            f32x4 fin = rb[0][lane];
+            for (int k = 1; k < KW; ++k) fin += rb[k][lane];
+            gemm_epilogue_t<EPI>(g, tile, lane, 0, fin, rstd_s, EpiPreT{});
         }
         return;
     }
 
     const int ks0 = (KS * kw) / KW, nks = (KS * (kw + 1)) / KW - ks0;  // nks <= KSW (checked on the host)
-    auto wptr = [&](int tile) -> const u32x4* {
-        int mi = 0, tl = tile;
-        if constexpr (EPI == kEpiScale || EPI == kEpiQkv) {
-            if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
-            if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
-        }
-        return reinterpret_cast<const u32x4*>(g.W[mi]) + ((size_t)tl * KS + ks0) * 64 + lane;
-    };
     u32x4 wb[NST][P];
     auto issue = [&](u32x4 (&buf)[P], int tile, int j) {  // stage j of `tile`: k-steps j*P .. j*P+P-1 of the slice
-        const u32x4* w = wptr(tile);
+        const u32x4* w = reinterpret_cast<const u32x4*>(g.W[0]) + ((size_t)tile * KS + ks0) * 64 + lane;
 #pragma unroll
         for (int u = 0; u < P; ++u) buf[u] = load_stream(w + (size_t)min(j * P + u, max(nks - 1, 0)) * 64);
     };
@@ -814,7 +670,7 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
 #pragma unroll
         for (int i = 0; i < NLD; ++i)
             if (lane + i * 64 < n_el) mine[lane + i * 64] = av[i];
-        if constexpr (kNeedsRstd) rstd_stash(g, ssv, tmp_s);
+        rstd_stash(g, ssv, tmp_s);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the region is private to this wavefront
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -831,8 +687,8 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
                 if (j * P + u < nks) {
 #pragma unroll
                     for (int h = 0; h < SPLIT; ++h)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(mine_r[((j * P + u) * SPLIT + h) * 4 * nr]),
-                                                                      as_bf16x8(wb[j][u]), acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[j][u]),
+                                                                      as_bf16x8(mine_r[((j * P + u) * SPLIT + h) * 4 * nr]), acc, 0, 0, 0);
                 }
             }
             if (next_tile < n_tiles) issue(wb[j], next_tile, j);  // refill what was just consumed
@@ -851,9 +707,9 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
 template <int KSW, int KW, int EPI, int P, int SPLIT>
 __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g) {
     static_assert(KSW % P == 0 && (KSW / P) % 2 == 0, "a tile must take an even number of register stages");
-    constexpr int NACC = 1;
+    static_assert(EPI == kEpiSwiglu || EPI == kEpiHead, "one matrix, an epilogue without inputs of its own");
     constexpr int NST = KSW / P;
-    __shared__ f32x4 red[2][KW][NACC][64];
+    __shared__ f32x4 red[2][KW][64];
     __shared__ float rstd_s[kMaxRows];
     __shared__ float tmp_s[KW * 64];
     const int kw = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -870,35 +726,20 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
             for (int h = 0; h < SPLIT; ++h) areg[i][h] = af[((size_t)(ks0 + min(i, max(nks - 1, 0))) * 2 + h) * 64];
     }
 
-    auto wptr = [&](int tile, int which) -> const u32x4* {
-        int mi = which, tl = tile;
-        if constexpr (EPI == kEpiScale || EPI == kEpiQkv) {
-            if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
-            if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
-        }
-        return reinterpret_cast<const u32x4*>(g.W[mi]) + ((size_t)tl * KS + ks0) * 64 + lane;
-    };
-    u32x4 wb[2][NACC][P];
-    auto issue = [&](u32x4 (&buf)[NACC][P], int tile, int j) {  // stage j of `tile`: k-steps j*P .. j*P+P-1 of the slice
+    u32x4 wb[2][P];
+    auto issue = [&](u32x4 (&buf)[P], int tile, int j) {  // stage j of `tile`: k-steps j*P .. j*P+P-1 of the slice
+        const u32x4* w = reinterpret_cast<const u32x4*>(g.W[0]) + ((size_t)tile * KS + ks0) * 64 + lane;
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) {
-            const u32x4* w = wptr(tile, a);
-#pragma unroll
-            for (int u = 0; u < P; ++u) buf[a][u] = load_stream(w + (size_t)min(j * P + u, nks - 1) * 64);
-        }
+        for (int u = 0; u < P; ++u) buf[u] = load_stream(w + (size_t)min(j * P + u, nks - 1) * 64);
     };
 
     int tile = blockIdx.x;
     if (tile < n_tiles && nks > 0) issue(wb[0], tile, 0);
-    if constexpr (EPI != kEpiResid) compute_rstd(g, rstd_s, tmp_s);
+    compute_rstd(g, rstd_s, tmp_s);
 
     for (int it = 0; tile < n_tiles; tile += gridDim.x, ++it) {
-        f32x4 acc[NACC];
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
         const int next_tile = tile + gridDim.x;
-        EpiPre pre;
-        if (kw == it % KW) epi_prefetch<EPI>(g, tile, lane, 0, pre);
 #pragma unroll
         for (int j = 0; j < NST; ++j) {
             // request the next stage (of this tile, or the first one of the next tile) before consuming this one
@@ -911,25 +752,17 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
                 if (j * P + u < nks) {
 #pragma unroll
                     for (int h = 0; h < SPLIT; ++h)
-#pragma unroll
-                        for (int a = 0; a < NACC; ++a)
-                            acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(areg[j * P + u][h]),
-                                                                             as_bf16x8(wb[j & 1][a][u]), acc[a], 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[j & 1][u]), as_bf16x8(areg[j * P + u][h]), acc, 0, 0, 0);
                 }
             }
         }
-        f32x4(&rb)[KW][NACC][64] = red[it & 1];
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) rb[kw][a][lane] = acc[a];
+        f32x4(&rb)[KW][64] = red[it & 1];
+        rb[kw][lane] = acc;
         __syncthreads();
         if (kw == it % KW) {
-            f32x4 fin[NACC];
-#pragma unroll
-            for (int a = 0; a < NACC; ++a) {
-                fin[a] = rb[0][a][lane];
-                for (int k = 1; k < KW; ++k) fin[a] += rb[k][a][lane];
-            }
-            gemm_epilogue<EPI, NACC>(g, tile, lane, 0, fin, rstd_s, pre);
+            f32x4 fin = rb[0][lane];
+            for (int k = 1; k < KW; ++k) fin += rb[k][lane];
+            gemm_epilogue_t<EPI>(g, tile, lane, 0, fin, rstd_s, EpiPreT{});
         }
     }
 }
