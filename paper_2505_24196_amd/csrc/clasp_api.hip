@@ -790,6 +790,23 @@ int dp_select_window(clasp_ctx* ctx, const float* states, size_t layer_stride, i
     return CLASP_OK;
 }
 
+// ---- cache contents in (LOAD) and out ----------------------------------------------------------------------------------
+template <bool LOAD>
+int launch_kv_move(const clasp_ctx* ctx, int layer, int pos0, int n, float* K, float* V, hipStream_t st) {
+    const clasp_config& c = ctx->cfg;
+    char *Kc = ctx->k_cache + (size_t)layer * ctx->kv_layer_bytes, *Vt = ctx->v_cache + (size_t)layer * ctx->kv_layer_bytes;
+    if (c.dtype == CLASP_BF16) {
+        const int aligned = (reinterpret_cast<uintptr_t>(K) & 15) == 0;  // the caller's rows: 16-byte pieces only if they are
+        hipLaunchKernelGGL(kv_move_kernel<LOAD>, dim3(2048), dim3(256), 0, st, K, V, reinterpret_cast<kv_t*>(Kc),
+                           reinterpret_cast<kv_t*>(Vt), pos0, n, c.n_kv_heads, c.head_dim, c.max_seq, aligned);
+    } else {
+        hipLaunchKernelGGL(kv_move_f32_kernel<LOAD>, dim3(1024), dim3(256), 0, st, K, V, reinterpret_cast<float*>(Kc),
+                           reinterpret_cast<float*>(Vt), pos0, n, c.n_kv_heads, c.head_dim, c.max_seq);
+    }
+    CLASP_LAUNCH_CHECK();
+    return CLASP_OK;
+}
+
 // ---- stochastic decoding --------------------------------------------------------------------------------------------
 // The draws' scratch is the attention's partial results, which no call needs beyond its own layers.
 SampleArgs sample_args(const clasp_ctx* ctx, float temperature) {
@@ -1319,16 +1336,7 @@ int clasp_kv_load(clasp_ctx* ctx, int layer, const float* K, const float* V, int
     if (layer < 0 || layer >= c.n_layers || n_tokens < 0 || n_tokens > c.max_seq) return CLASP_E_INVALID_ARG;
     if (n_tokens == 0) return CLASP_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    void* Kc = ctx->k_cache + (size_t)layer * ctx->kv_layer_bytes;
-    void* Vt = ctx->v_cache + (size_t)layer * ctx->kv_layer_bytes;
-    if (c.dtype == CLASP_BF16)
-        hipLaunchKernelGGL((kv_load_kernel<kDtBf16>), dim3(1024), dim3(256), 0, st, K, V, Kc, Vt, n_tokens, c.n_kv_heads,
-                           c.head_dim, c.max_seq);
-    else
-        hipLaunchKernelGGL((kv_load_kernel<kDtF32>), dim3(1024), dim3(256), 0, st, K, V, Kc, Vt, n_tokens, c.n_kv_heads,
-                           c.head_dim, c.max_seq);
-    CLASP_LAUNCH_CHECK();
-    return CLASP_OK;
+    return launch_kv_move<true>(ctx, layer, 0, n_tokens, const_cast<float*>(K), const_cast<float*>(V), st);
 }
 
 int clasp_kv_read(clasp_ctx* ctx, int layer, int pos0, int n_tokens, float* K, float* V, void* stream) {
@@ -1338,16 +1346,7 @@ int clasp_kv_read(clasp_ctx* ctx, int layer, int pos0, int n_tokens, float* K, f
         return CLASP_E_INVALID_ARG;
     if (n_tokens == 0) return CLASP_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const void* Kc = ctx->k_cache + (size_t)layer * ctx->kv_layer_bytes;
-    const void* Vt = ctx->v_cache + (size_t)layer * ctx->kv_layer_bytes;
-    if (c.dtype == CLASP_BF16)
-        hipLaunchKernelGGL((kv_read_kernel<kDtBf16>), dim3(1024), dim3(256), 0, st, Kc, Vt, K, V, pos0, n_tokens,
-                           c.n_kv_heads, c.head_dim, c.max_seq);
-    else
-        hipLaunchKernelGGL((kv_read_kernel<kDtF32>), dim3(1024), dim3(256), 0, st, Kc, Vt, K, V, pos0, n_tokens,
-                           c.n_kv_heads, c.head_dim, c.max_seq);
-    CLASP_LAUNCH_CHECK();
-    return CLASP_OK;
+    return launch_kv_move<false>(ctx, layer, pos0, n_tokens, K, V, st);
 }
 
 int clasp_verify_forward(clasp_ctx* ctx, const int32_t* tokens, int n_tokens, int pos0, float* hidden_out,

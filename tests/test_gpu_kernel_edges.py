@@ -211,3 +211,34 @@ def test_greedy_head_and_small_projections(vocab, d, ffn):
     want = torch.softmax(q.double(), 0).max().item()
     assert abs(float(prob) / want - 1) <= 1e-5  # one rescaling and a tree of sums: about 20 roundings of 6e-8
     eng.close()
+
+
+# Cache contents in and out at the edges of 32-position blocks and 8-position pieces, from and to buffers that are not 16-byte
+# aligned: every value comes back exactly, and positions outside the call's range keep what they held.
+@pytest.mark.parametrize("dtype,kv,hd", [("bf16", 2, 64), ("bf16", 3, 128), ("f32", 2, 16)])
+def test_cache_moves_at_block_edges(dtype, kv, hd):
+    import paper_2505_24196_amd as clasp
+    shape = si.ModelShape("edge-kv", 2, 64, kv, kv, hd, 64, 112, dtype) if dtype == "bf16" else \
+        si.ModelShape("edge-kv", 2, 32, kv, kv, hd, 64, 112, dtype)
+    eng = clasp.Engine(shape, max_seq=160, max_rows=4).load(si.gen_model(shape, 3, "cpu"))
+    ref = [torch.zeros(160, kv, hd, device="cuda") for _ in range(2)]
+    for off in (0, 1):  # element offset of the caller's buffers
+        for T in (1, 7, 8, 31, 32, 33, 100, 160):
+            bufs = [torch.randn(160 * kv * hd + off, device="cuda").half().float() for _ in range(2)]
+            src = [b[off:off + T * kv * hd] for b in bufs]
+            rc = clasp.lib().clasp_kv_load(eng._ctx, 1, src[0].data_ptr(), src[1].data_ptr(), T, None)
+            assert rc == 0
+            torch.cuda.synchronize()
+            for r, s in zip(ref, src):
+                r[:T] = s.view(T, kv, hd)
+            for pos0, n in ((0, 160), (T - 1, 161 - T), (5, 29), (32, 32), (40, 1), (63, 66)):
+                n = min(n, 160 - pos0)
+                out = [torch.full((160 * kv * hd + off + 64,), -7.0, device="cuda") for _ in range(2)]
+                rc = clasp.lib().clasp_kv_read(eng._ctx, 1, pos0, n, out[0].data_ptr() + 4 * off, out[1].data_ptr() + 4 * off, None)
+                assert rc == 0
+                torch.cuda.synchronize()
+                for o, r in zip(out, ref):
+                    assert torch.equal(o[off:off + n * kv * hd].view(n, kv, hd), r[pos0:pos0 + n]), (off, T, pos0, n)
+                    assert (o[:off] == -7).all() and (o[off + n * kv * hd:] == -7).all()
+    assert all((t == 0).all() for t in eng.clasp_kv_read(0, 0, 160))  # the other layer
+    eng.close()
