@@ -130,8 +130,7 @@ __device__ __forceinline__ void attn_softmax(AttnState<HD, NT>& st, f32x4 (&s)[2
         for (int u = 0; u < 2; ++u)
 #pragma unroll
             for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[u][t][r]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        mx = max32(max16(mx));
         m_new[t] = fmaxf(st.m[t], mx);
         m_safe[t] = (m_new[t] == -INFINITY) ? 0.f : m_new[t];
         grew = grew || m_new[t] > st.m[t];
@@ -304,8 +303,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         float l = st.l[t];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = add32(add16(l));
         if (lane < 16) {
             mg_m[wave][lane] = st.m[t];
             mg_l[wave][lane] = l;
@@ -478,8 +476,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
         return (qv[0] * k[0] + qv[1] * k[1]) + (qv[2] * k[2] + qv[3] * k[3]);
     };
     auto score = [&](float s, int t) {  // the four lanes of a key add up
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
+        s += dpp<kDppXor1>(s);
+        s += dpp<kDppXor2>(s);
         s *= a.scale;
         if (sub == 0) sc[t] = s;
         mx = fmaxf(mx, s);

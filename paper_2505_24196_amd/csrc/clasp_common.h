@@ -72,26 +72,53 @@ __device__ __forceinline__ u32x4 as_u32x4(bf16x8 v) { return __builtin_bit_cast(
 // small activation working set that every workgroup re-reads from L2.
 __device__ __forceinline__ u32x4 load_stream(const u32x4* p) { return __builtin_nontemporal_load(p); }
 
-// Sum over the 16 lanes that share lane/16 (xor butterflies stay inside the 16-lane row).
+// ---- across lanes -------------------------------------------------------------------------------------------------------
+// On the vector units instead of through LDS (__shfl_xor is a ds_bpermute, some 60 cycles of latency, and the short kernels
+// end in chains of them): within 16 lanes the DPP patterns quad_perm and (half) row mirror, which after the steps before
+// them bring every lane the partial result of the other half; across 16 and 32 lanes gfx950's permlane swaps, which leave
+// the two halves side by side. Every lane combines the same values, in the same order, as with an xor butterfly.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
+
+// The values of a lane and of the one 16 (32) lanes away, lower lane first in both.
+__device__ __forceinline__ float2 pair16(float v) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float2 pair32(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return make_float2(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float add16(float v) { const float2 p = pair16(v); return p.x + p.y; }
+__device__ __forceinline__ float add32(float v) { const float2 p = pair32(v); return p.x + p.y; }
+__device__ __forceinline__ float max16(float v) { const float2 p = pair16(v); return fmaxf(p.x, p.y); }
+__device__ __forceinline__ float max32(float v) { const float2 p = pair32(v); return fmaxf(p.x, p.y); }
+// The value of the lane 32 away.
+__device__ __forceinline__ float other32(float v) {
+    const float2 p = pair32(v);
+    return (threadIdx.x & 32) ? p.x : p.y;
+}
+
+// Sum over the 16 lanes that share lane/16.
 __device__ __forceinline__ float sum16(float v) {
-    v += __shfl_xor(v, 1);
-    v += __shfl_xor(v, 2);
-    v += __shfl_xor(v, 4);
-    v += __shfl_xor(v, 8);
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);
+    v += dpp<kDppMirror>(v);
     return v;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-    v = sum16(v);
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
-}
+__device__ __forceinline__ float wave_sum(float v) { return add32(add16(sum16(v))); }
 
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
-    return v;
+    v = fmaxf(v, dpp<kDppXor1>(v));
+    v = fmaxf(v, dpp<kDppXor2>(v));
+    v = fmaxf(v, dpp<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp<kDppMirror>(v));
+    return max32(max16(v));
 }
 
 // Deterministic block-wide sum (fixed tree): every thread gets the total. `scratch` holds >= blockDim/64 floats.

@@ -250,7 +250,7 @@ __device__ __forceinline__ void qkv_epilogue_t(const GemmArgs& g, int tile, int 
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         own[i] = sum[i] * rs;
-        partner[i] = __shfl_xor(own[i], 32);
+        partner[i] = other32(own[i]);
     }
     if (row >= g.n_rows) return;
     if (which == 2) {  // v: plain feature order
@@ -313,8 +313,7 @@ __device__ __forceinline__ void gemm_epilogue_t(const GemmArgs& g, int tile, int
         }
         if (g.next_ss) {
             float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-            sq += __shfl_xor(sq, 16);
-            sq += __shfl_xor(sq, 32);
+            sq = add32(add16(sq));
             if (live && lane < 16) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
         }
     } else if constexpr (EPI == kEpiSwiglu) {
@@ -324,7 +323,7 @@ __device__ __forceinline__ void gemm_epilogue_t(const GemmArgs& g, int tile, int
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float own = sum[i] * rs, up = __shfl_xor(own, 32);
+            const float own = sum[i] * rs, up = other32(own);
             v[i] = own / (1.0f + expf(-own)) * up;
         }
         if (live && lane < 32) store_operand4<kDtBf16>(g.next_op, g.R, 0, row, tile * 8 + (lane >> 4) * 4, v);
@@ -343,8 +342,7 @@ __device__ __forceinline__ void gemm_epilogue_t(const GemmArgs& g, int tile, int
             top2_merge(v1, i1, v2, b1, bi, b2);
         }
         float se = (expf(x[0] - v1) + expf(x[1] - v1)) + (expf(x[2] - v1) + expf(x[3] - v1));
-        se += __shfl_xor(se, 16);
-        se += __shfl_xor(se, 32);
+        se = add32(add16(se));
         if (live && lane < 16) g.head_parts[(size_t)row * (g.N >> 4) + tile] = f32x4{v1, __int_as_float(i1), v2, se};
     }
 }
@@ -901,8 +899,7 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
         }
         if (g.next_ss) {
             float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-            sq += __shfl_xor(sq, 16);
-            sq += __shfl_xor(sq, 32);
+            sq = add32(add16(sq));
             if (lane < 16) g.next_ss[(size_t)tile * kMaxRows + row] = sq;
         }
     } else {

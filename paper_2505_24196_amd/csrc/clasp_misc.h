@@ -276,19 +276,16 @@ __device__ __forceinline__ void select_cell(const SelectArgs& a, int j, float (*
         if constexpr (HAS_COMP) g = load_comp(c);
         dots(x4[c], skip4[c], g);
     }
-    const int wave = tid >> 6, nw = blockDim.x >> 6;
+    const int wave = tid >> 6;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
         acc[k] = wave_sum(acc[k]);
         if ((tid & 63) == 0) red[wave][k] = acc[k];
     }
     __syncthreads();
+    // sixteen wavefronts: every 16 lanes add their sums up once more
 #pragma unroll
-    for (int k = 0; k < 5; ++k) {
-        float t = 0.f;
-        for (int w = 0; w < nw; ++w) t += red[w][k];
-        acc[k] = t;
-    }
+    for (int k = 0; k < 5; ++k) acc[k] = sum16(red[tid & 15][k]);
     const float nx = fmaxf(sqrtf(acc[0]), 1e-12f);
     const float sig_s = acc[1] / (fmaxf(sqrtf(acc[2]), 1e-12f) * nx);
     const float sig_c = HAS_COMP ? acc[3] / (fmaxf(sqrtf(acc[4]), 1e-12f) * nx) : __builtin_nanf("");
@@ -306,8 +303,8 @@ __device__ __forceinline__ void select_cell(const SelectArgs& a, int j, float (*
         if (feeds) {
             store_operand4<DT>(a.op, a.R, d, j - a.jn0, c * 4, v * gn);
             float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];  // 4 lanes cover one 16-column tile
-            sq += __shfl_xor(sq, 1);
-            sq += __shfl_xor(sq, 2);
+            sq += dpp<kDppXor1>(sq);
+            sq += dpp<kDppXor2>(sq);
             if ((c & 3) == 0) a.ss[(size_t)(c >> 2) * kMaxRows + (j - a.jn0)] = sq;
         }
     };

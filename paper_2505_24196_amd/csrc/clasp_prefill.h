@@ -81,9 +81,9 @@ struct RowBlock {
     __device__ float row_sum(float v, float* red) const {
         if constexpr (!F16) return block_sum(v, red);
         const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        v += __shfl_xor(v, 1);
-        v += __shfl_xor(v, 2);
-        v += __shfl_xor(v, 4);
+        v += dpp<kDppXor1>(v);
+        v += dpp<kDppXor2>(v);
+        v += dpp<kDppHalfMirror>(v);
         if ((lane & 7) == 0) red[wave * 8 + (lane >> 3)] = v;
         __syncthreads();
         float t = 0.f;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillGemmArgs& p, int r
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             own[r] = acc[r] * rstd;
-            partner[r] = __shfl_xor(own[r], 32);
+            partner[r] = other32(own[r]);
         }
         if (!live) return;
         const int pos = o.pos0 + row;
@@ -228,15 +228,14 @@ __device__ __forceinline__ void prefill_epilogue(const PrefillGemmArgs& p, int r
         if (g.next_op) store_operand4_fmt(g.next_op, g.R, row, col0, v * gain, p.op_f16);  // rows that do not exist: zeros
         // sum of squares over the tile's 16 features: the lane's four, then the four lanes of the row
         float sq = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
-        sq += __shfl_xor(sq, 16);
-        sq += __shfl_xor(sq, 32);
+        sq = add32(add16(sq));
         if (g.next_ss && f0 == 0 && live) g.next_ss[(size_t)tile * p.ld_ss + row] = sq;
     } else {  // kEpiSwiglu: features 0..7 of a tile are gate features 8*tile .., features 8..15 the matching up features
         f32x4 v;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float own = acc[r] * rstd;  // 0 for a row that does not exist
-            const float up = __shfl_xor(own, 32);
+            const float up = other32(own);
             v[r] = live ? own / (1.0f + expf(-own)) * up : 0.f;
         }
         if (f0 < 8) store_operand4_fmt(g.next_op, g.R, row, tile * 8 + f0, v, p.op_f16);
@@ -635,8 +634,7 @@ __global__ __launch_bounds__(kPrefillAttnWaves * 64) void prefill_attn_kernel(Pr
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         float l = st.l[t];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = add32(add16(l));
         const int qi = (t0 + t) * 16 + m16;
         if (qi >= nQ) continue;
         const float inv = 1.0f / l;
@@ -769,8 +767,7 @@ __global__ __launch_bounds__(NW * 64) void prefill_attn_lds_kernel(PrefillAttnAr
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         float l = st.l[t];
-        l += __shfl_xor(l, 16);
-        l += __shfl_xor(l, 32);
+        l = add32(add16(l));
         const int qi = (t0 + t) * 16 + m16;
         if (qi >= nQ) continue;
         const float inv = 1.0f / l;
