@@ -23,6 +23,7 @@ def build(force: bool = True, verbose: bool = False, extra_flags=(), out: str = 
         return LIB
     cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",  # no packed-fp32 code generation
+           "-mllvm", "-amdgpu-kernarg-preload-count=14",  # leading scalar arguments arrive in registers
            "-Wno-unused-command-line-argument", "-o", out] + list(extra_flags) + SOURCES
     if verbose:
         print(" ".join(cmd))

@@ -344,7 +344,7 @@ int launch_gemv(const TimerScope& timer, const GemmArgs& g, size_t lds, hipStrea
             return CLASP_E_HIP;
         opted_in = true;
     }
-    launch_timed(timer, kernel, dim3(g.N / 16), dim3(KWV * 64), lds, st, g, (g.K / 32 + KWV - 1) / KWV);
+    launch_timed(timer, kernel, dim3(g.N / 16), dim3(KWV * 64), lds, st, GEMM_LEAD_ARGS(g), g, (g.K / 32 + KWV - 1) / KWV);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
@@ -363,7 +363,7 @@ int launch_few_rows(const clasp_ctx* ctx, const TimerScope& timer, const GemmArg
     }
     const int tiles = g.N / 16, rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
     launch_timed(timer, kernel, dim3(grid), dim3((kResidentKW + 1) * 64),
-                 (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * g.n_rows, st, g);
+                 (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * g.n_rows, st, GEMM_LEAD_ARGS(g), g);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
@@ -385,7 +385,7 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
         const int rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
         if constexpr (EPI == kEpiSwiglu || EPI == kEpiHead)
             launch_timed(timer, gemm_bf16_resident_kernel<kResidentKSW, kResidentKW, EPI, CLASP_GEMM_DEPTH, CLASP_ACT_SPLIT>,
-                         dim3(grid), dim3(kResidentKW * 64), 0, st, g);
+                         dim3(grid), dim3(kResidentKW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
     } else if (gemv_lds) {
         if constexpr (EPI == kEpiResid) {
             if (g.attn_partial) return launch_gemv<EPI, KWV, 1>(timer, g, gemv_lds, st);
@@ -398,8 +398,8 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
             // per wavefront and two K slices (22 workgroups, four trips), 6.1 us. With more tiles than CUs those
             // wider workgroups win: their wavefronts share the activation loads.
             if (tiles <= ctx->n_cu) {
-                if (g.R == 1) launch_timed(timer, gemm_bf16_kernel<1, 1, 8, EPI, CLASP_STREAM_DEPTH, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
-                else launch_timed(timer, gemm_bf16_kernel<2, 1, 8, EPI, 4, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, g);
+                if (g.R == 1) launch_timed(timer, gemm_bf16_kernel<1, 1, 8, EPI, CLASP_STREAM_DEPTH, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, GEMM_LEAD_ARGS(g), g);
+                else launch_timed(timer, gemm_bf16_kernel<2, 1, 8, EPI, 4, CLASP_ACT_SPLIT, 1>, dim3(tiles), dim3(512), 0, st, GEMM_LEAD_ARGS(g), g);
                 CLASP_LAUNCH_CHECK();
                 return CLASP_OK;
             }
@@ -410,7 +410,7 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
             if (g.R == 1 && tiles >= 2 * ctx->n_cu) {
                 constexpr int WN = CLASP_QKV_WIDE_NACC;
                 launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / WN, CLASP_ACT_SPLIT, WN>,
-                             dim3((tiles + CW * WN - 1) / (CW * WN)), dim3(CW * KW * 64), 0, st, g);
+                             dim3((tiles + CW * WN - 1) / (CW * WN)), dim3(CW * KW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
                 CLASP_LAUNCH_CHECK();
                 return CLASP_OK;
             }
@@ -418,13 +418,13 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
         if (g.R == 1) {  // NACC tiles per wavefront share the activation fragments; the stage depth shrinks to match
             const dim3 grid((tiles + CW * NACC - 1) / (CW * NACC));
             launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / NACC, CLASP_ACT_SPLIT, NACC>, grid,
-                         dim3(CW * KW * 64), 0, st, g);
+                         dim3(CW * KW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
         } else {
             // two row groups: R2NACC column tiles per wavefront share the four activation loads of a k-step (weight
             // fragments per stage stay the same, so fewer tiles per wavefront mean more k-steps per stage)
             const dim3 grid((tiles + R2CW * R2NACC - 1) / (R2CW * R2NACC));
             launch_timed(timer, gemm_bf16_kernel<2, R2CW, R2KW, EPI, CLASP_R2_DEPTH * CLASP_R2_NACC / R2NACC, CLASP_ACT_SPLIT, R2NACC>,
-                         grid, dim3(R2CW * R2KW * 64), 0, st, g);
+                         grid, dim3(R2CW * R2KW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
         }
     }
     CLASP_LAUNCH_CHECK();
@@ -439,8 +439,8 @@ int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kin
         else return launch_gemm_bf16<EPI, CW, KW, NACC, R2NACC, R2CW, R2KW>(ctx, timer, g, st, kind);
     }
     if constexpr (EPI == kEpiQkv || EPI == kEpiHead || EPI == kEpiPartial) return CLASP_E_UNSUPPORTED;  // bf16 models only
-    else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(g.N / 16), dim3(512), 0, st, g);
-    else launch_timed(timer, gemm_f32_kernel<EPI, 2>, dim3(g.N / 16), dim3(512), 0, st, g);
+    else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(g.N / 16), dim3(512), 0, st, GEMM_LEAD_ARGS(g), g);
+    else launch_timed(timer, gemm_f32_kernel<EPI, 2>, dim3(g.N / 16), dim3(512), 0, st, GEMM_LEAD_ARGS(g), g);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
@@ -455,7 +455,7 @@ int launch_attn_one(const AttnArgs& a, dim3 grid, hipStream_t st) {
             return CLASP_E_HIP;
         opted_in = true;
     }
-    hipLaunchKernelGGL((attn_bf16_kernel<HD, NT, NW, STREAM>), grid, dim3(NW * 64), lds, st, a);
+    hipLaunchKernelGGL((attn_bf16_kernel<HD, NT, NW, STREAM>), grid, dim3(NW * 64), lds, st, ATTN_LEAD_ARGS(a), a);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
@@ -520,7 +520,7 @@ int launch_attention(const clasp_ctx* ctx, int layer, int n, int R, int mode, in
                 return CLASP_E_HIP;
             opted = true;
         }
-        hipLaunchKernelGGL(kernel, dim3(c.n_heads, n), dim3(256), lds, st, a);
+        hipLaunchKernelGGL(kernel, dim3(c.n_heads, n), dim3(256), lds, st, ATTN_F32_LEAD_ARGS(a), a);
         CLASP_LAUNCH_CHECK();
         return CLASP_OK;
     }
@@ -636,12 +636,12 @@ int run_layer(const clasp_ctx* ctx, int l, int n, int R, int mode, int pos0, con
             launch_timed(timer, gemm_bf16_kernel<1, CLASP_DOWNP_CW, CLASP_DOWNP_KW, kEpiPartial,
                                                  CLASP_STREAM_DEPTH / CLASP_DOWNP_NACC, CLASP_ACT_SPLIT, CLASP_DOWNP_NACC>,
                          dim3((d / 16 + CLASP_DOWNP_CW * CLASP_DOWNP_NACC - 1) / (CLASP_DOWNP_CW * CLASP_DOWNP_NACC), down_split),
-                         block, 0, st, g);
+                         block, 0, st, GEMM_LEAD_ARGS(g), g);
         else
             launch_timed(timer, gemm_bf16_kernel<2, CLASP_DOWNP_CW, CLASP_DOWNP_KW, kEpiPartial, CLASP_R2_DEPTH,
                                                  CLASP_ACT_SPLIT, CLASP_R2_NACC>,
                          dim3((d / 16 + CLASP_DOWNP_CW * CLASP_R2_NACC - 1) / (CLASP_DOWNP_CW * CLASP_R2_NACC), down_split),
-                         block, 0, st, g);
+                         block, 0, st, GEMM_LEAD_ARGS(g), g);
         CLASP_LAUNCH_CHECK();
     } else {
         GemmArgs g{};
@@ -779,9 +779,11 @@ int dp_select_window(clasp_ctx* ctx, const float* states, size_t layer_stride, i
         s.scores = score_out; s.choice = choice;
         const int cells_i = ((i < M) ? i : M) + 1 - j0;
         if (c.dtype == CLASP_BF16)
-            hipLaunchKernelGGL((dp_select_kernel<kDtBf16>), dim3(cells_i), dim3(1024), 0, st, s);
+            hipLaunchKernelGGL((dp_select_kernel<kDtBf16>), dim3(cells_i), dim3(1024), 0, st, s.x_i, s.g_prev, s.G, s.parts, s.d, s.i,
+                               s.M, s.n_parts, s.j0, s.jc0, s);
         else
-            hipLaunchKernelGGL((dp_select_kernel<kDtF32>), dim3(cells_i), dim3(1024), 0, st, s);
+            hipLaunchKernelGGL((dp_select_kernel<kDtF32>), dim3(cells_i), dim3(1024), 0, st, s.x_i, s.g_prev, s.G, s.parts, s.d, s.i,
+                               s.M, s.n_parts, s.j0, s.jc0, s);
         CLASP_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(dp_backtrack_kernel, dim3(2), dim3(256), 0, st, choice, L, M, mask_out, lo, c.n_layers,

@@ -40,6 +40,17 @@ struct AttnArgs {
     const void* v_self;
 };
 
+// The scalars that the attention kernels need first, preloaded like those of the GEMM kernels.
+#define ATTN_LEAD_PARAMS                                                                                            \
+    const void *lead_q, const void *lead_k, const void *lead_v, int lead_pos0, int lead_rows, int lead_heads,        \
+        int lead_kv_heads, int lead_t_max, int lead_mode, int lead_split
+#define ATTN_LEAD_ARGS(a) (a).q_frag, (a).Kc, (a).Vt, (a).pos0, (a).n_rows, (a).n_heads, (a).n_kv_heads, (a).t_max, (a).mode, (a).n_split
+#define ATTN_F32_LEAD_PARAMS                                                                                        \
+    const float *lead_qkv, const void *lead_k, const void *lead_v, const float2 *lead_rope, int lead_ld, int lead_hd, \
+        int lead_pos0, int lead_t_max, int lead_heads, int lead_kv_heads
+#define ATTN_F32_LEAD_ARGS(a) \
+    (a).qkv, (a).Kc, (a).Vt, (a).rope, (a).ld_qkv, (a).head_dim, (a).pos0, (a).t_max, (a).n_heads, (a).n_kv_heads
+
 #ifndef CLASP_ATTN_DOUBLE_NT
 #define CLASP_ATTN_DOUBLE_NT 1  // query tiles up to which a workgroup keeps two whole fragment sets
 #endif
@@ -189,7 +200,7 @@ __device__ __forceinline__ void attn_compute(AttnState<HD, NT>& st, const kvx8 (
 // q_frag: queries of one KV head (query index qi = row*group + head%group) as MFMA B fragments,
 // [kv_head][qi/16][x/32][lane = ((x%32)/8)*16 + qi%16][x%8], written by the q/k/v projection's epilogue.
 template <int HD, int NT, int NW, bool STREAM>
-__global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
+__global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(ATTN_LEAD_PARAMS, AttnArgs a) {
     constexpr int KK = HD / 32, CT = HD / 16;
     extern __shared__ float lds_dyn[];  // NW*HD*17 floats: per-wavefront O^T tiles (+1 column against bank conflicts)
     typedef float (*MgT)[HD][17];
@@ -197,16 +208,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     __shared__ float mg_m[NW][16], mg_l[NW][16], mg_f[NW][16];
     const int kvh = blockIdx.x, qg = blockIdx.y, split = blockIdx.z;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int G = a.n_heads / a.n_kv_heads, nQ = a.n_rows * G;
+    const int G = lead_heads / lead_kv_heads, nQ = lead_rows * G;
     const int q_base = qg * NT * 16;
     const int m16 = lane & 15, q4 = lane >> 4;
-    const kv_t* Kc = reinterpret_cast<const kv_t*>(a.Kc);
-    const kv_t* Vt = reinterpret_cast<const kv_t*>(a.Vt);
+    const kv_t* Kc = reinterpret_cast<const kv_t*>(lead_k);
+    const kv_t* Vt = reinterpret_cast<const kv_t*>(lead_v);
 
     // query fragments straight from HBM/L2 (already rotated, scaled and in B-operand order)
     kvx8 qf[NT][KK];
     {
-        const u32x4* qp = reinterpret_cast<const u32x4*>(a.q_frag) + ((size_t)kvh * (2 * G) + qg * NT) * KK * 64 + lane;
+        const u32x4* qp = reinterpret_cast<const u32x4*>(lead_q) + ((size_t)kvh * (2 * G) + qg * NT) * KK * 64 + lane;
 #pragma unroll
         for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -220,7 +231,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     for (int t = 0; t < NT; ++t) {
         const int qi = q_base + t * 16 + m16;
         qrow[t] = qi < nQ ? qi / G : -1;
-        limit[t] = qi < nQ ? (a.mode ? a.pos0 + qrow[t] : a.pos0 - 1) : -1;
+        limit[t] = qi < nQ ? (lead_mode ? lead_pos0 + qrow[t] : lead_pos0 - 1) : -1;
     }
 
     AttnState<HD, NT> st;
@@ -232,11 +243,11 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
         for (int c = 0; c < CT; ++c) st.o[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    const int n_cache = a.pos0 + (a.mode ? a.n_rows : 0);  // cache positions any row may see
+    const int n_cache = lead_pos0 + (lead_mode ? lead_rows : 0);  // cache positions any row may see
     const int nblk = (n_cache + 31) >> 5;
-    const int b0 = (int)(((long long)nblk * split) / a.n_split), b1 = (int)(((long long)nblk * (split + 1)) / a.n_split);
-    const u32x4* Kh = reinterpret_cast<const u32x4*>(Kc + (size_t)kvh * a.t_max * HD) + lane;
-    const u32x4* Vh = reinterpret_cast<const u32x4*>(Vt + (size_t)kvh * a.t_max * HD) + lane;
+    const int b0 = (int)(((long long)nblk * split) / lead_split), b1 = (int)(((long long)nblk * (split + 1)) / lead_split);
+    const u32x4* Kh = reinterpret_cast<const u32x4*>(Kc + (size_t)kvh * lead_t_max * HD) + lane;
+    const u32x4* Vh = reinterpret_cast<const u32x4*>(Vt + (size_t)kvh * lead_t_max * HD) + lane;
     auto load_blk = [&](AttnFrags<HD>& f, int blk) {
         const u32x4* kp = Kh + (size_t)blk * (2 * KK * 64);
         const u32x4* vp = Vh + (size_t)blk * (CT * 64);
@@ -289,7 +300,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
             if (blk + NW < b1) load_v(blk + NW);
         }
     }
-    if (!a.mode && split == a.n_split - 1 && wave == (b1 - b0) % NW) {  // DP candidates: own key/value only
+    if (!lead_mode && split == lead_split - 1 && wave == (b1 - b0) % NW) {  // DP candidates: own key/value only
         const u32x4* kp = reinterpret_cast<const u32x4*>(a.k_self) + (size_t)kvh * (2 * KK * 64) + lane;
         const u32x4* vp = reinterpret_cast<const u32x4*>(a.v_self) + (size_t)kvh * (CT * 64) + lane;
         AttnFrags<HD> f;
@@ -299,7 +310,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
     }
 
     // merge the wavefronts' running (max, sum, O^T), one query tile at a time, fixed order
-    float* part = a.partial + ((((size_t)kvh * gridDim.y + qg) * a.n_split + split) * NT * 16) * (HD + 2);
+    float* part = a.partial + ((((size_t)kvh * gridDim.y + qg) * lead_split + split) * NT * 16) * (HD + 2);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         float l = st.l[t];
@@ -332,7 +343,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bf16_kernel(AttnArgs a) {
             if (qi < nQ) {
                 float O = 0.f;
                 for (int w = 0; w < NW; ++w) O += mg_f[w][j] * mg_o[w][e][j];
-                if (a.n_split == 1) {
+                if (lead_split == 1) {
                     const int row = qi / G, h = kvh * G + qi % G;
                     store_operand<kDtBf16>(a.out_op, a.R, 0, row, h * HD + e, O / mg_l[0][j]);
                 } else {
@@ -408,23 +419,23 @@ constexpr size_t attn_f32_lds_floats(int head_dim, int pos0, int n_rows) {
     return (size_t)head_dim * (2 + 2 * n_rows) + pos0 + 32 + 4;
 }
 template <bool VEC>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256) void attn_f32_kernel(ATTN_F32_LEAD_PARAMS, AttnArgs a) {
     extern __shared__ __align__(16) float lds[];
     __shared__ float red[8];
-    const int h = blockIdx.x, r = blockIdx.y, HD = a.head_dim, HALF = HD / 2;
-    const int G = a.n_heads / a.n_kv_heads, kvh = h / G;
-    const int pos = a.pos0 + (a.mode ? r : 0);
+    const int h = blockIdx.x, r = blockIdx.y, HD = lead_hd, HALF = HD / 2;
+    const int G = lead_heads / lead_kv_heads, kvh = h / G;
+    const int pos = lead_pos0 + (a.mode ? r : 0);
     const int n_self = a.mode ? r + 1 : 1;  // visible self keys: rows 0..r, or only row r
     const int self0 = a.mode ? 0 : r;
-    const int n_keys = a.pos0 + n_self;
+    const int n_keys = lead_pos0 + n_self;
     const int tid = threadIdx.x, lane = tid & 63, sub = tid & 3, l16 = tid & 15, g16 = tid >> 4, key = tid >> 2;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* q = lds;                        // [HD], then the n_self own keys, then the n_self own values
     float* own_k = q + HD;
     float* own_v = own_k + n_self * HD;
     float* sc = lds + (HD * (1 + 2 * n_self) + 3) / 4 * 4;  // [n_keys]
-    const float* Kc = reinterpret_cast<const float*>(a.Kc) + (size_t)kvh * a.t_max * HD;
-    const float* Vt = reinterpret_cast<const float*>(a.Vt) + (size_t)kvh * HD * a.t_max;
+    const float* Kc = reinterpret_cast<const float*>(lead_k) + (size_t)kvh * lead_t_max * HD;
+    const float* Vt = reinterpret_cast<const float*>(lead_v) + (size_t)kvh * HD * lead_t_max;
     const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
     // rows 0 (query), 1..n_self (own keys), n_self+1.. (own values), a wavefront each, as rotary pairs (e, e + HALF)
     const int rows = 1 + 2 * n_self;
@@ -432,9 +443,9 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     auto fetch = [&](int row, int e) -> Pair {
         const int kind = row == 0 ? 0 : (row <= n_self ? 1 : 2);
         const int sr = kind == 0 ? r : self0 + (row - 1) - (kind == 2 ? n_self : 0);
-        const int head = kind == 0 ? h : a.n_heads + kvh + (kind == 2 ? a.n_kv_heads : 0);
-        const float* p = a.qkv + (size_t)sr * a.ld_qkv + head * HD + e;
-        const float2 cs = a.rope[(size_t)(a.pos0 + (a.mode ? sr : 0)) * HALF + e];
+        const int head = kind == 0 ? h : lead_heads + kvh + (kind == 2 ? lead_kv_heads : 0);
+        const float* p = lead_qkv + (size_t)sr * lead_ld + head * HD + e;
+        const float2 cs = lead_rope[(size_t)(lead_pos0 + (a.mode ? sr : 0)) * HALF + e];
         return Pair{p[0], p[HALF], kind < 2 ? cs : make_float2(1.f, 0.f)};
     };
     auto stash = [&](const Pair& p, int row, int e) {
@@ -449,17 +460,17 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int u = 0; u < kRows; ++u) pr[u] = fetch(min(wave + 4 * u, rows - 1), e0);
     auto load_v = [&](int e, int t) {  // positions t .. t+3; those at or beyond pos0 are not this call's to use
-        f32x4 v = *reinterpret_cast<const f32x4*>(Vt + (size_t)e * a.t_max + t);
+        f32x4 v = *reinterpret_cast<const f32x4*>(Vt + (size_t)e * lead_t_max + t);
 #pragma unroll
-        for (int u = 1; u < 4; ++u) v[u] = t + u < a.pos0 ? v[u] : 0.f;
+        for (int u = 1; u < 4; ++u) v[u] = t + u < lead_pos0 ? v[u] : 0.f;
         return v;
     };
     if constexpr (VEC) {
 #pragma unroll
         for (int i = 0; i < kPre; ++i) {
             const int e = (i * 4 + sub) * 4, ev = i * 16 + g16;
-            kpre[i] = key < a.pos0 && e < HD ? *reinterpret_cast<const f32x4*>(Kc + (size_t)key * HD + e) : zero;
-            vpre[i] = l16 * 4 < a.pos0 && ev < HD ? load_v(ev, l16 * 4) : zero;
+            kpre[i] = key < lead_pos0 && e < HD ? *reinterpret_cast<const f32x4*>(Kc + (size_t)key * HD + e) : zero;
+            vpre[i] = l16 * 4 < lead_pos0 && ev < HD ? load_v(ev, l16 * 4) : zero;
         }
     }
 #pragma unroll
@@ -483,7 +494,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
         mx = fmaxf(mx, s);
     };
 #pragma unroll 1
-    for (int t = key; t < a.pos0; t += 64) {
+    for (int t = key; t < lead_pos0; t += 64) {
         float s = 0.f;
         const float* kp = Kc + (size_t)t * HD;
         if constexpr (VEC) {
@@ -505,7 +516,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
         float s = 0.f;
 #pragma unroll 4
         for (int e = sub; e < HD; e += 4) s = fmaf(q[e], own_k[key * HD + e], s);
-        score(s, a.pos0 + key);
+        score(s, lead_pos0 + key);
     }
     mx = wave_max(mx);
     if (lane == 0) red[wave] = mx;
@@ -527,7 +538,7 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     float first[kPre];
     if constexpr (VEC) {
 #pragma unroll
-        for (int i = 0; i < kPre; ++i) first[i] = l16 * 4 < a.pos0 ? pv4(vpre[i], l16 * 4) : 0.f;
+        for (int i = 0; i < kPre; ++i) first[i] = l16 * 4 < lead_pos0 ? pv4(vpre[i], l16 * 4) : 0.f;
     }
 #pragma unroll 1
     for (int i = 0; i * 16 < HD; ++i) {
@@ -541,21 +552,21 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
                     t += 64;
                 }
 #pragma unroll 4
-                for (; t < a.pos0; t += 64) o += pv4(load_v(e, t), t);
+                for (; t < lead_pos0; t += 64) o += pv4(load_v(e, t), t);
             } else {
-                for (int t = l16; t < a.pos0; t += 16) o = fmaf(sc[t], Vt[(size_t)e * a.t_max + t], o);
+                for (int t = l16; t < lead_pos0; t += 16) o = fmaf(sc[t], Vt[(size_t)e * lead_t_max + t], o);
             }
-            for (int k = l16; k < n_self; k += 16) o = fmaf(sc[a.pos0 + k], own_v[k * HD + e], o);
+            for (int k = l16; k < n_self; k += 16) o = fmaf(sc[lead_pos0 + k], own_v[k * HD + e], o);
         }
         o = sum16(o);
-        if (e < HD && l16 == 0) store_operand<kDtF32>(a.out_op, a.R, a.n_heads * HD, r, h * HD + e, o / den);
+        if (e < HD && l16 == 0) store_operand<kDtF32>(a.out_op, a.R, lead_heads * HD, r, h * HD + e, o / den);
     }
     if (a.mode && h % G == 0) {  // this row's key/value into the cache: the last of the own ones
-        float* Kw = reinterpret_cast<float*>(a.Kc) + ((size_t)kvh * a.t_max + pos) * HD;
-        float* Vw = reinterpret_cast<float*>(a.Vt) + (size_t)kvh * HD * a.t_max + pos;
+        float* Kw = reinterpret_cast<float*>(a.Kc) + ((size_t)kvh * lead_t_max + pos) * HD;
+        float* Vw = reinterpret_cast<float*>(a.Vt) + (size_t)kvh * HD * lead_t_max + pos;
         for (int e = tid; e < HD; e += 256) {
             Kw[e] = own_k[r * HD + e];
-            Vw[(size_t)e * a.t_max] = own_v[r * HD + e];
+            Vw[(size_t)e * lead_t_max] = own_v[r * HD + e];
         }
     }
 }

@@ -74,6 +74,15 @@ struct GemmArgs {
     int attn_split, attn_group, attn_hd;
 };
 
+// What a GEMM kernel needs for its first loads, passed as scalars in front of the argument struct: the library is built
+// with kernel-argument preloading (the first 14 dwords arrive in scalar registers with the workgroup), while a struct is
+// fetched from memory by every workgroup before it can compute an address. At 4-10 us per kernel that fetch is
+// worth 0.35 us a launch (tiny fp32 model, verify pass 237 -> 224 us).
+#define GEMM_LEAD_PARAMS                                                                                             \
+    const void *lead_w0, const void *lead_w1, const void *lead_w2, const void *lead_a, int lead_k, int lead_rows,    \
+        int lead_end0, int lead_end1
+#define GEMM_LEAD_ARGS(g) (g).W[0], (g).W[1], (g).W[2], (g).A, (g).K, (g).n_rows, (g).tile_end[0], (g).tile_end[1]
+
 // (largest, index, second largest) of two disjoint sets; equal maxima keep the lower index.
 __device__ __forceinline__ void top2_merge(float& a1, int& ai, float& a2, float b1, int bi, float b2) {
     if (b1 > a1 || (b1 == a1 && bi < ai)) {
@@ -355,7 +364,7 @@ __device__ __forceinline__ void gemm_epilogue_t(const GemmArgs& g, int tile, int
 // (Cross-workgroup split-K inside one kernel is not used: agent-scope release fences cost far more than they save
 // on this part, every one of them writes the whole L2 back.)
 template <int R, int CW, int KW, int EPI, int P, int SPLIT, int NACC = 1>
-__global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GEMM_LEAD_PARAMS, GemmArgs g) {
     constexpr int NW = CW * KW;
     __shared__ f32x4 red[KW][CW][NACC][R][64];
     __shared__ float rstd_s[kMaxRows];
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
     const int cw = wave % CW, kw = wave / CW;
     const int n_tiles = g.N >> 4;
     const int tile0 = (blockIdx.x * CW + cw) * NACC;
-    const int KS = g.K >> 5;
+    const int KS = lead_k >> 5;
     const int nslice = gridDim.y * KW, slice = blockIdx.y * KW + kw;  // gridDim.y > 1 only with kEpiPartial
     const int ks0 = (int)(((long long)KS * slice) / nslice), ks1 = (int)(((long long)KS * (slice + 1)) / nslice);
 
@@ -375,16 +384,16 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
         tile[a] = min(tile0 + a, n_tiles - 1);  // tiles beyond the last shadow it, their result is dropped
         int mi = 0, tl = tile[a];
         if constexpr (EPI == kEpiQkv) {
-            if (tile[a] >= g.tile_end[0]) { mi = 1; tl = tile[a] - g.tile_end[0]; }
-            if (tile[a] >= g.tile_end[1]) { mi = 2; tl = tile[a] - g.tile_end[1]; }
+            if (tile[a] >= lead_end0) { mi = 1; tl = tile[a] - lead_end0; }
+            if (tile[a] >= lead_end1) { mi = 2; tl = tile[a] - lead_end1; }
         }
-        w[a] = reinterpret_cast<const u32x4*>(g.W[mi]) + (size_t)tl * KS * 64 + lane;
+        w[a] = reinterpret_cast<const u32x4*>(mi == 0 ? lead_w0 : mi == 1 ? lead_w1 : lead_w2) + (size_t)tl * KS * 64 + lane;
     }
     const u32x4* af[R];
 #pragma unroll
     for (int rg = 0; rg < R; ++rg) {  // row of this lane, clamped to the last live row; may sit in an earlier group
-        const int row = min(rg * 16 + (lane & 15), g.n_rows - 1);
-        af[rg] = reinterpret_cast<const u32x4*>(g.A) + (size_t)(row >> 4) * 128 + (row & 15) * 4 + (lane >> 4);
+        const int row = min(rg * 16 + (lane & 15), lead_rows - 1);
+        af[rg] = reinterpret_cast<const u32x4*>(lead_a) + (size_t)(row >> 4) * 128 + (row & 15) * 4 + (lane >> 4);
     }
 
     f32x4 acc[NACC][R];
@@ -462,22 +471,22 @@ __global__ __launch_bounds__(CW * KW * 64) void gemm_bf16_kernel(GemmArgs g) {
 constexpr int kGemvLoads = 8;
 constexpr int kGemvMaxSplit = 8;
 template <int KW, int EPI, int P, int SPLIT, int ASRC = 0>
-__global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_max) {
+__global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GEMM_LEAD_PARAMS, GemmArgs g, int nks_max) {
     extern __shared__ u32x4 a_lds[];
     __shared__ f32x4 red[KW][64];
     __shared__ float rstd_s[kMaxRows];
     __shared__ float tmp_s[KW * 64];
     constexpr bool kNeedsRstd = EPI != kEpiResid && EPI != kEpiPartial;
     const int kw = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
-    const int tile = blockIdx.x, KS = g.K >> 5;
+    const int tile = blockIdx.x, KS = lead_k >> 5;
     const int ks0 = (KS * kw) / KW, ks1 = (KS * (kw + 1)) / KW, nks = ks1 - ks0;
 
     int mi = 0, tl = tile;
     if constexpr (EPI == kEpiQkv) {
-        if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
-        if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
+        if (tile >= lead_end0) { mi = 1; tl = tile - lead_end0; }
+        if (tile >= lead_end1) { mi = 2; tl = tile - lead_end1; }
     }
-    const u32x4* w0 = reinterpret_cast<const u32x4*>(g.W[mi]) + (size_t)tl * KS * 64 + lane;
+    const u32x4* w0 = reinterpret_cast<const u32x4*>(mi == 0 ? lead_w0 : mi == 1 ? lead_w1 : lead_w2) + (size_t)tl * KS * 64 + lane;
     u32x4 wb[2][P];
     auto issue = [&](u32x4 (&buf)[P], int s) {
 #pragma unroll
@@ -493,7 +502,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
     float ssv[16];
     if constexpr (ASRC == 0) {
         u32x4 av[kGemvLoads];
-        const u32x4* A = reinterpret_cast<const u32x4*>(g.A);
+        const u32x4* A = reinterpret_cast<const u32x4*>(lead_a);
 #pragma unroll
         for (int i = 0; i < kGemvLoads; ++i) {
             const int e = min(lane + i * 64, max(n_el - 1, 0));
@@ -611,7 +620,7 @@ __global__ __launch_bounds__(KW * 64) void gemv_bf16_kernel(GemmArgs g, int nks_
 // LDS, and an epilogue has two tile times to finish). Needs K/32 <= KW*KSW.
 constexpr int kFewRows = 8;
 template <int KSW, int KW, int EPI, int P, int SPLIT>
-__global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(GemmArgs g) {
+__global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(GEMM_LEAD_PARAMS, GemmArgs g) {
     static_assert(KSW % P == 0, "a tile slice is a whole number of stages");
     static_assert(EPI == kEpiSwiglu || EPI == kEpiHead, "one matrix, and both need the rows' 1/rms");
     constexpr int NST = KSW / P;
@@ -620,7 +629,7 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
     __shared__ float rstd_s[kMaxRows];
     __shared__ float tmp_s[(KW + 1) * 64];
     const int kw = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane >> 4;
-    const int n_tiles = g.N >> 4, KS = g.K >> 5;
+    const int n_tiles = g.N >> 4, KS = lead_k >> 5;
     float ssv[16];
     rstd_issue(g, ssv);
 
@@ -641,7 +650,7 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
     const int ks0 = (KS * kw) / KW, nks = (KS * (kw + 1)) / KW - ks0;  // nks <= KSW (checked on the host)
     u32x4 wb[NST][P];
     auto issue = [&](u32x4 (&buf)[P], int tile, int j) {  // stage j of `tile`: k-steps j*P .. j*P+P-1 of the slice
-        const u32x4* w = reinterpret_cast<const u32x4*>(g.W[0]) + ((size_t)tile * KS + ks0) * 64 + lane;
+        const u32x4* w = reinterpret_cast<const u32x4*>(lead_w0) + ((size_t)tile * KS + ks0) * 64 + lane;
 #pragma unroll
         for (int u = 0; u < P; ++u) buf[u] = load_stream(w + (size_t)min(j * P + u, max(nks - 1, 0)) * 64);
     };
@@ -652,11 +661,11 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
     }
     // the live rows of this wavefront's k-slice into its LDS region: piece e = ((k-step, plane, 16-byte quarter), row),
     // row fastest, so that the 16 lanes of a quarter read 16 consecutive pieces
-    const int nr = g.n_rows;
+    const int nr = lead_rows;
     u32x4* mine = a_s + (size_t)kw * (KSW * SPLIT * 4) * nr;
     {
         const int n_el = nks * SPLIT * 4 * nr;
-        const u32x4* A = reinterpret_cast<const u32x4*>(g.A);
+        const u32x4* A = reinterpret_cast<const u32x4*>(lead_a);
         constexpr int NLD = (KSW * SPLIT * 4 * kFewRows + 63) / 64;
         u32x4 av[NLD];
 #pragma unroll
@@ -703,7 +712,7 @@ __global__ __launch_bounds__((KW + 1) * 64) void gemv_persistent_bf16_kernel(Gem
 // current tile's last ones are consumed), the per-tile reduction over the KW slices goes through a double-buffered
 // LDS tile with one barrier per tile, and the epilogue duty rotates over the wavefronts.
 template <int KSW, int KW, int EPI, int P, int SPLIT>
-__global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g) {
+__global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GEMM_LEAD_PARAMS, GemmArgs g) {
     static_assert(KSW % P == 0 && (KSW / P) % 2 == 0, "a tile must take an even number of register stages");
     static_assert(EPI == kEpiSwiglu || EPI == kEpiHead, "one matrix, an epilogue without inputs of its own");
     constexpr int NST = KSW / P;
@@ -711,13 +720,13 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
     __shared__ float rstd_s[kMaxRows];
     __shared__ float tmp_s[KW * 64];
     const int kw = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int n_tiles = g.N >> 4, KS = g.K >> 5;
+    const int n_tiles = g.N >> 4, KS = lead_k >> 5;
     const int ks0 = (KS * kw) / KW, nks = (KS * (kw + 1)) / KW - ks0;  // nks <= KSW (checked on the host)
 
     // this wavefront's slice of the activations, resident for the whole kernel
     u32x4 areg[KSW][SPLIT];
     {
-        const u32x4* af = reinterpret_cast<const u32x4*>(g.A) + min(lane & 15, g.n_rows - 1) * 4 + (lane >> 4);
+        const u32x4* af = reinterpret_cast<const u32x4*>(lead_a) + min(lane & 15, lead_rows - 1) * 4 + (lane >> 4);
 #pragma unroll
         for (int i = 0; i < KSW; ++i)  // rows that do not exist mirror the last live row, steps beyond the slice its last step
 #pragma unroll
@@ -726,7 +735,7 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
 
     u32x4 wb[2][P];
     auto issue = [&](u32x4 (&buf)[P], int tile, int j) {  // stage j of `tile`: k-steps j*P .. j*P+P-1 of the slice
-        const u32x4* w = reinterpret_cast<const u32x4*>(g.W[0]) + ((size_t)tile * KS + ks0) * 64 + lane;
+        const u32x4* w = reinterpret_cast<const u32x4*>(lead_w0) + ((size_t)tile * KS + ks0) * 64 + lane;
 #pragma unroll
         for (int u = 0; u < P; ++u) buf[u] = load_stream(w + (size_t)min(j * P + u, nks - 1) * 64);
     };
@@ -777,7 +786,7 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GemmArgs g)
 // 32 rows and 32 x 6 shuffles per feature; 4.1 us (projections onto d), 5.2 (q, k, v) and 6.6 (gate and up) now. Error
 // against 64 bits as before (2.8e-7 after eight layers).
 template <int EPI, int R>
-__global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
+__global__ __launch_bounds__(512) void gemm_f32_kernel(GEMM_LEAD_PARAMS, GemmArgs g) {
     constexpr int KW = 8, NACC = (EPI == kEpiSwiglu) ? 2 : 1, P = 4;
     constexpr bool kNeedsRstd = EPI != kEpiResid;
     __shared__ f32x4 red[KW][NACC][R][64];
@@ -785,22 +794,22 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
     __shared__ float tmp_s[KW * 64];
     const int tile = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int c = lane & 15, q4 = lane >> 4;
-    const int KS = g.K >> 4;  // K % 16 == 0 (checked at create)
+    const int KS = lead_k >> 4;  // K % 16 == 0 (checked at create)
     const int ks0 = (KS * wave) / KW, ks1 = (KS * (wave + 1)) / KW;
     int mi = 0, tl = tile;
     if constexpr (EPI == kEpiScale) {
-        if (tile >= g.tile_end[0]) { mi = 1; tl = tile - g.tile_end[0]; }
-        if (tile >= g.tile_end[1]) { mi = 2; tl = tile - g.tile_end[1]; }
+        if (tile >= lead_end0) { mi = 1; tl = tile - lead_end0; }
+        if (tile >= lead_end1) { mi = 2; tl = tile - lead_end1; }
     }
     const f32x4* w[NACC];
 #pragma unroll
     for (int a = 0; a < NACC; ++a)
-        w[a] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.W[NACC == 2 ? a : mi]) +
-                                              ((size_t)tl * 16 + c) * g.K) + q4;
+        w[a] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(NACC == 2 ? (a ? lead_w1 : lead_w0) : (mi == 0 ? lead_w0 : mi == 1 ? lead_w1 : lead_w2)) +
+                                              ((size_t)tl * 16 + c) * lead_k) + q4;
     const f32x4* x[R];  // lanes of rows that do not exist read the last live row, their results are dropped
 #pragma unroll
     for (int rg = 0; rg < R; ++rg)
-        x[rg] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(g.A) + (size_t)min(rg * 16 + c, g.n_rows - 1) * g.K) + q4;
+        x[rg] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(lead_a) + (size_t)min(rg * 16 + c, lead_rows - 1) * lead_k) + q4;
 
     f32x4 acc[NACC][R][4];
 #pragma unroll
@@ -845,7 +854,7 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
     if constexpr (EPI == kEpiResid) {
         if (wave < R) {
             if (g.next_gain) gain = *reinterpret_cast<const f32x4*>(g.next_gain + col0);
-            if (row < g.n_rows) resid = *reinterpret_cast<const f32x4*>(g.resid + (size_t)row * g.ldr + col0);
+            if (row < lead_rows) resid = *reinterpret_cast<const f32x4*>(g.resid + (size_t)row * g.ldr + col0);
         }
     }
     while (s < ks1) {
@@ -877,7 +886,7 @@ __global__ __launch_bounds__(512) void gemm_f32_kernel(GemmArgs g) {
 #pragma unroll
         for (int k = 1; k < KW; ++k) sum[a] += red[k][a][wave][lane];
     }
-    const bool live = row < g.n_rows;
+    const bool live = row < lead_rows;
     auto store4 = [](float* base, int ld, int r, int col, const f32x4& v) {  // a caller's buffer may not be 16-byte aligned
         float* p = base + (size_t)r * ld + col;
         if ((reinterpret_cast<uintptr_t>(base) & 15) == 0 && (ld & 3) == 0) {

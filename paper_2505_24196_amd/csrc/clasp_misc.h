@@ -323,7 +323,12 @@ __device__ __forceinline__ void select_cell(const SelectArgs& a, int j, float (*
 }
 
 template <int DT>
-__global__ __launch_bounds__(1024) void dp_select_kernel(SelectArgs a) {
+__global__ __launch_bounds__(1024) void dp_select_kernel(const float* lead_x, const float* lead_prev, const float* lead_g,
+                                                         const float* lead_parts, int lead_d, int lead_i, int lead_m, int lead_n,
+                                                         int lead_j0, int lead_jc0, SelectArgs a) {
+    // (preloaded scalars, see GEMM_LEAD_PARAMS)
+    a.x_i = lead_x; a.g_prev = lead_prev; a.G = lead_g; a.parts = lead_parts;
+    a.d = lead_d; a.i = lead_i; a.M = lead_m; a.n_parts = lead_n; a.j0 = lead_j0; a.jc0 = lead_jc0;
     __shared__ float red[16][5];
     const int j = a.j0 + blockIdx.x, d = a.d;
     if (j == 0) {
