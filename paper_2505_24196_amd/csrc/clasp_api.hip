@@ -115,16 +115,6 @@ void* static_scratch_ptr() {
 #ifndef CLASP_R2_DEPTH
 #define CLASP_R2_DEPTH 2  // k-steps per register stage of those launches
 #endif
-// ... per projection (tiles per wavefront, column-tile wavefronts, K-slice wavefronts of a two-group launch)
-#ifndef CLASP_R2_OPROJ
-#define CLASP_R2_OPROJ 2, 1, 8
-#endif
-#ifndef CLASP_R2_GATEUP
-#define CLASP_R2_GATEUP CLASP_R2_NACC, CLASP_GATEUP_CW, CLASP_GATEUP_KW
-#endif
-#ifndef CLASP_R2_QKV
-#define CLASP_R2_QKV 4, 1, 4
-#endif
 // k-steps per register stage (two stages in flight)
 #ifndef CLASP_STREAM_DEPTH
 #define CLASP_STREAM_DEPTH 8  // several-row streaming kernel, one row group
@@ -368,7 +358,7 @@ int launch_few_rows(const clasp_ctx* ctx, const TimerScope& timer, const GemmArg
     return CLASP_OK;
 }
 
-template <int EPI, int CW, int KW, int NACC, int R2NACC, int R2CW, int R2KW>
+template <int EPI, int CW, int KW, int NACC>
 int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmArgs& g, hipStream_t st, int kind) {
     const int tiles = g.N / 16;
     // gate|up and lm_head on one row group, K short enough for its rows to stay on the CU, more tiles than CUs
@@ -420,23 +410,48 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
             launch_timed(timer, gemm_bf16_kernel<1, CW, KW, EPI, CLASP_STREAM_DEPTH / NACC, CLASP_ACT_SPLIT, NACC>, grid,
                          dim3(CW * KW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
         } else {
-            // two row groups: R2NACC column tiles per wavefront share the four activation loads of a k-step (weight
-            // fragments per stage stay the same, so fewer tiles per wavefront mean more k-steps per stage)
-            const dim3 grid((tiles + R2CW * R2NACC - 1) / (R2CW * R2NACC));
-            launch_timed(timer, gemm_bf16_kernel<2, R2CW, R2KW, EPI, CLASP_R2_DEPTH * CLASP_R2_NACC / R2NACC, CLASP_ACT_SPLIT, R2NACC>,
-                         grid, dim3(R2CW * R2KW * 64), 0, st, GEMM_LEAD_ARGS(g), g);
+            // two row groups: the column tiles of a wavefront share the four activation loads of a k-step, as long as that
+            // leaves the CUs enough workgroups (NA tiles per wavefront, CA column-tile wavefronts, KA K slices, PA k-steps
+            // per register stage)
+            auto launch_two = [&](auto na, auto ca, auto ka, auto pa) {
+                constexpr int NA = decltype(na)::value, CA = decltype(ca)::value, KA = decltype(ka)::value, PA = decltype(pa)::value;
+                launch_timed(timer, gemm_bf16_kernel<2, CA, KA, EPI, PA, CLASP_ACT_SPLIT, NA>, dim3((tiles + CA * NA - 1) / (CA * NA)),
+                             dim3(CA * KA * 64), 0, st, GEMM_LEAD_ARGS(g), g);
+            };
+            using std::integral_constant;
+            using I1 = integral_constant<int, 1>;
+            using I2 = integral_constant<int, 2>;
+            using I4 = integral_constant<int, 4>;
+            using I8 = integral_constant<int, 8>;
+            if constexpr (EPI == kEpiResid) {
+                // projections onto d_model: two tiles from 2 x CUs tiles on (70B shape, 512 tiles: 7196 us per search with two,
+                // 7249 with one), one below (8B shape, 256 tiles, verify pass of 24 rows on six layers: 1160 us with one, 1219
+                // with two, 1265 with two and four, which also spilled registers)
+                if (tiles >= 2 * ctx->n_cu) launch_two(I2{}, I1{}, I8{}, I2{});
+                else launch_two(I1{}, I1{}, I8{}, I4{});
+            } else if constexpr (EPI == kEpiSwiglu) {
+                // four wavefronts of four tiles when that makes a workgroup for three quarters of the CUs (70B shape, 224
+                // workgroups: 7250 us per search, 7294 with two), else two and twice the K slices (8B shape, 112 -> 224
+                // workgroups: 1145 -> 1032 us for the pass above)
+                if ((tiles + 15) / 16 * 4 >= 3 * ctx->n_cu) launch_two(I4{}, I4{}, I2{}, I2{});
+                else launch_two(I4{}, I2{}, I4{}, I2{});
+            } else if constexpr (EPI == kEpiQkv) {
+                launch_two(I4{}, I1{}, I4{}, I2{});
+            } else {
+                launch_two(I4{}, I4{}, I2{}, I2{});
+            }
         }
     }
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
 
-template <int EPI, int CW, int KW, int NACC = 1, int R2NACC = CLASP_R2_NACC, int R2CW = CW, int R2KW = KW>
+template <int EPI, int CW, int KW, int NACC = 1>
 int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kind) {
     TimerScope timer(ctx, kind, st, false);
     if (ctx->cfg.dtype == CLASP_BF16) {
         if constexpr (EPI == kEpiScale) return CLASP_E_UNSUPPORTED;  // fp32 models only
-        else return launch_gemm_bf16<EPI, CW, KW, NACC, R2NACC, R2CW, R2KW>(ctx, timer, g, st, kind);
+        else return launch_gemm_bf16<EPI, CW, KW, NACC>(ctx, timer, g, st, kind);
     }
     if constexpr (EPI == kEpiQkv || EPI == kEpiHead || EPI == kEpiPartial) return CLASP_E_UNSUPPORTED;  // bf16 models only
     else if (g.R == 1) launch_timed(timer, gemm_f32_kernel<EPI, 1>, dim3(g.N / 16), dim3(512), 0, st, GEMM_LEAD_ARGS(g), g);
@@ -594,7 +609,7 @@ int run_layer(const clasp_ctx* ctx, int l, int n, int R, int mode, int pos0, con
             o.k_cache = ctx->k_cache + (size_t)l * ctx->kv_layer_bytes;
             o.v_cache = ctx->v_cache + (size_t)l * ctx->kv_layer_bytes;
             o.k_self = ctx->k_self; o.v_self = ctx->v_self;
-            if ((rc = launch_gemm<kEpiQkv, CLASP_QKV_CW, CLASP_QKV_KW, CLASP_QKV_NACC, CLASP_R2_QKV>(ctx, g, st, CLASP_KERNEL_QKV))) return rc;
+            if ((rc = launch_gemm<kEpiQkv, CLASP_QKV_CW, CLASP_QKV_KW, CLASP_QKV_NACC>(ctx, g, st, CLASP_KERNEL_QKV))) return rc;
         } else {
             if ((rc = launch_gemm<kEpiScale, 1, 1>(ctx, g, st, CLASP_KERNEL_QKV))) return rc;
         }
@@ -610,7 +625,7 @@ int run_layer(const clasp_ctx* ctx, int l, int n, int R, int mode, int pos0, con
         }
         g.out = ctx->a_buf; g.ldo = d; g.resid = h_in; g.ldr = d;
         g.next_op = ctx->op_a; g.next_gain = ctx->mlp_norm[l]; g.next_ss = ctx->ss_a;
-        if ((rc = launch_gemm<kEpiResid, CLASP_OPROJ_CW, CLASP_OPROJ_KW, CLASP_OPROJ_NACC, CLASP_R2_OPROJ>(ctx, g, st, CLASP_KERNEL_O_PROJ))) return rc;
+        if ((rc = launch_gemm<kEpiResid, CLASP_OPROJ_CW, CLASP_OPROJ_KW, CLASP_OPROJ_NACC>(ctx, g, st, CLASP_KERNEL_O_PROJ))) return rc;
     }
     {
         GemmArgs g{};
@@ -623,7 +638,7 @@ int run_layer(const clasp_ctx* ctx, int l, int n, int R, int mode, int pos0, con
         g.A = ctx->op_a; g.n_rows = n; g.K = d; g.R = R;
         g.ss_parts = ctx->ss_a; g.n_parts = d / 16; g.inv_dim = 1.0f / d; g.eps = c.rms_eps;
         g.next_op = ctx->op_act;
-        if ((rc = launch_gemm<kEpiSwiglu, CLASP_GATEUP_CW, CLASP_GATEUP_KW, CLASP_GATEUP_NACC, CLASP_R2_GATEUP>(ctx, g, st, CLASP_KERNEL_GATE_UP))) return rc;
+        if ((rc = launch_gemm<kEpiSwiglu, CLASP_GATEUP_CW, CLASP_GATEUP_KW, CLASP_GATEUP_NACC>(ctx, g, st, CLASP_KERNEL_GATE_UP))) return rc;
     }
     if (down_split > 1 && c.dtype == CLASP_BF16) {
         GemmArgs g{};
