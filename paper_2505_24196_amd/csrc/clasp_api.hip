@@ -1061,12 +1061,16 @@ int launch_prefill_attn(const clasp_ctx* ctx, const PrefillAttnArgs& a, hipStrea
         if (c.head_dim == 64) return launch(prefill_attn_lds_kernel<64, NW>, (size_t)kPrefillAttnStages * 8 * 1024, opted_in[0]);
         return launch(prefill_attn_lds_kernel<128, NW>, (size_t)kPrefillAttnStages * 16 * 1024, opted_in[1]);
     }
-    const int per_wg = kPrefillAttnWaves * kPrefillAttnNT;
-    const dim3 grid(c.n_kv_heads, (n_qt + per_wg - 1) / per_wg);
-    if (c.head_dim == 64) hipLaunchKernelGGL(prefill_attn_kernel<64>, grid, dim3(kPrefillAttnWaves * 64), 0, st, a);
-    else hipLaunchKernelGGL(prefill_attn_kernel<128>, grid, dim3(kPrefillAttnWaves * 64), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    return CLASP_OK;
+    // two query tiles per wavefront share its key and value reads, one makes twice the workgroups: one until two cover the CUs
+    auto launch = [&](auto kernel, int nt) -> int {
+        const int per_wg = kPrefillAttnWaves * nt;
+        hipLaunchKernelGGL(kernel, dim3(c.n_kv_heads, (n_qt + per_wg - 1) / per_wg), dim3(kPrefillAttnWaves * 64), 0, st, a);
+        CLASP_LAUNCH_CHECK();
+        return CLASP_OK;
+    };
+    if (c.n_kv_heads * ((n_qt + kPrefillAttnWaves * 2 - 1) / (kPrefillAttnWaves * 2)) < ctx->n_cu)
+        return c.head_dim == 64 ? launch(prefill_attn_kernel<64, 1>, 1) : launch(prefill_attn_kernel<128, 1>, 1);
+    return c.head_dim == 64 ? launch(prefill_attn_kernel<64, 2>, 2) : launch(prefill_attn_kernel<128, 2>, 2);
 }
 
 // The full model over n rows at positions pos0.. (n <= the chunk the workspace was carved for): leaves their keys and
