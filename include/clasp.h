@@ -137,8 +137,8 @@ int clasp_verify_forward(clasp_ctx *ctx, const int32_t *tokens, int n_tokens, in
  * rows or more (chunk_rows >= 640 and that many rows left) run their projections on fp16 matrix instructions: each
  * activation is rounded to one fp16 number (11 significant bits instead of the pair's 16; values beyond +-65504, which
  * an un-normalised hidden state times its gain or a SwiGLU product of a trained model may in principle reach, saturate
- * there instead of becoming infinities), the layer's weights are converted to fp16 into the workspace at the start of
- * the layer (exact for every bf16 weight of magnitude >= 2^-17, rounding to multiples of 2^-24 below), accumulation
+ * there instead of becoming infinities), the weights are converted to fp16 into the workspace layer by
+ * layer (exact for every bf16 weight of magnitude >= 2^-17, rounding to multiples of 2^-24 below), accumulation
  * stays fp32, attention is the same fp16 kernel family as elsewhere. That halves the matrix-core work of a pass; the
  * cache stays inside the 2e-2 of the fp64 reference that every result of a bf16 model is held to.
  *   tokens       dev int32 [n_tokens]; ids outside [0, vocab) are clamped

@@ -1040,13 +1040,19 @@ int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStrea
 #ifndef CLASP_PREFILL_ATTN_LDS_MIN_BLOCKS
 #define CLASP_PREFILL_ATTN_LDS_MIN_BLOCKS 32
 #endif
-int launch_prefill_attn(const clasp_ctx* ctx, const PrefillAttnArgs& a, hipStream_t st) {
+// Conversion workgroups behind an attention launch, per CU: small enough to fill the gaps that the attention's leave. 8B shape,
+// 1100 rows behind 1900 (144 attention workgroups), eight layers: 4 per CU 5.53 ms, 8: 5.49, 16: 5.48, 32: 5.52.
+constexpr int kConvertPerCu = 16;
+int launch_prefill_attn(const clasp_ctx* ctx, PrefillAttnArgs a, hipStream_t st) {
     const clasp_config& c = ctx->cfg;
     const int n_qt = a.R * ctx->group;
     const int nblk = (a.pos0 + a.n_rows + 31) / 32;
+    // workgroups that convert weights, in whole rows of the grid
+    const int convert_rows = a.convert.end[5] ? (ctx->n_cu * kConvertPerCu + c.n_kv_heads - 1) / c.n_kv_heads : 0;
     if (CLASP_PREFILL_ATTN_LDS_WAVES && nblk >= CLASP_PREFILL_ATTN_LDS_MIN_BLOCKS) {
         constexpr int NW = CLASP_PREFILL_ATTN_LDS_WAVES ? CLASP_PREFILL_ATTN_LDS_WAVES : 4;
-        const dim3 grid(c.n_kv_heads, (n_qt + NW * kPrefillAttnNT - 1) / (NW * kPrefillAttnNT));
+        a.q_blocks = (n_qt + NW * kPrefillAttnNT - 1) / (NW * kPrefillAttnNT);
+        const dim3 grid(c.n_kv_heads, a.q_blocks + convert_rows);
         static bool opted_in[2] = {false, false};
         auto launch = [&](auto kernel, size_t lds, bool& opted) -> int {
             if (!opted) {
@@ -1064,7 +1070,8 @@ int launch_prefill_attn(const clasp_ctx* ctx, const PrefillAttnArgs& a, hipStrea
     // two query tiles per wavefront share its key and value reads, one makes twice the workgroups: one until two cover the CUs
     auto launch = [&](auto kernel, int nt) -> int {
         const int per_wg = kPrefillAttnWaves * nt;
-        hipLaunchKernelGGL(kernel, dim3(c.n_kv_heads, (n_qt + per_wg - 1) / per_wg), dim3(kPrefillAttnWaves * 64), 0, st, a);
+        a.q_blocks = (n_qt + per_wg - 1) / per_wg;
+        hipLaunchKernelGGL(kernel, dim3(c.n_kv_heads, a.q_blocks + convert_rows), dim3(kPrefillAttnWaves * 64), 0, st, a);
         CLASP_LAUNCH_CHECK();
         return CLASP_OK;
     };
@@ -1095,25 +1102,42 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
         return f16 ? launch_prefill_gemm<EPI, true>(ctx, p, st, parts, part_rows)
                    : launch_prefill_gemm<EPI, false>(ctx, p, st, parts, part_rows);
     };
-    for (int l = 0; l < L; ++l) {
-        // this layer's matrices, as packed or as the fp16 copy made here (the last layer only runs q/k/v)
-        const void* W[6] = {ctx->wq[l], ctx->wk[l], ctx->wv[l], ctx->wo[l], ctx->w_gate_up[l], ctx->w_down[l]};
-        if (f16) {
-            const size_t bytes[6] = {(size_t)ctx->q_dim * d * 2, (size_t)ctx->kv_dim * d * 2, (size_t)ctx->kv_dim * d * 2,
-                                     (size_t)d * ctx->q_dim * 2, (size_t)2 * F * d * 2,       (size_t)d * F * 2};
-            const int n_mat = l == L - 1 ? 3 : 6;
-            ConvertArgs cv{};
-            size_t off = 0;
-            for (int m = 0; m < 6; ++m) {
-                cv.src[m] = static_cast<const u32x4*>(W[m]);
-                cv.dst[m] = reinterpret_cast<u32x4*>(ws.w16 + off);
-                if (m < n_mat) off += bytes[m];
-                cv.end[m] = off / 16;
-                W[m] = cv.dst[m];
-            }
-            hipLaunchKernelGGL(prefill_convert_f16_kernel, dim3(ctx->n_cu * 8), dim3(256), 0, st, cv);
-            CLASP_LAUNCH_CHECK();
+    // fp16 copies: one layer's room. Layer 0's q/k/v are converted here; the other three matrices of a layer and the next
+    // layer's q/k/v (whose place is free by then) by the attention launch in between.
+    u32x4* w16[6] = {};
+    auto conversion = [&](int l_qkv, int l_rest) {
+        const bool rest = l_rest >= 0;
+        const size_t qd = (size_t)ctx->q_dim * d, kvd = (size_t)ctx->kv_dim * d, fd = (size_t)F * d;
+        const int order[6] = {0, 1, 2, 5, 4, 3};  // what is read first (o_proj) is written last
+        const void* src[6] = {ctx->wq[l_qkv], ctx->wk[l_qkv], ctx->wv[l_qkv], rest ? ctx->wo[l_rest] : nullptr,
+                              rest ? ctx->w_gate_up[l_rest] : nullptr, rest ? ctx->w_down[l_rest] : nullptr};
+        const size_t units[6] = {qd / 8, kvd / 8, kvd / 8, qd / 8, 2 * fd / 8, fd / 8};
+        ConvertArgs cv{};
+        size_t end = 0;
+        for (int m = 0; m < 6; ++m) {
+            cv.src[m] = static_cast<const u32x4*>(src[order[m]]);
+            cv.dst[m] = w16[order[m]];
+            if (cv.src[m]) end += units[order[m]];
+            cv.end[m] = end;
         }
+        return cv;
+    };
+    if (f16) {
+        const size_t bytes[6] = {(size_t)ctx->q_dim * d * 2, (size_t)ctx->kv_dim * d * 2, (size_t)ctx->kv_dim * d * 2,
+                                 (size_t)d * ctx->q_dim * 2, (size_t)2 * F * d * 2,       (size_t)d * F * 2};
+        size_t off = 0;
+        for (int m = 0; m < 6; ++m) {
+            w16[m] = reinterpret_cast<u32x4*>(ws.w16 + off);
+            off += bytes[m];
+        }
+        hipLaunchKernelGGL(prefill_convert_f16_kernel, dim3(ctx->n_cu * 8), dim3(256), 0, st, conversion(0, -1));
+        CLASP_LAUNCH_CHECK();
+    }
+    for (int l = 0; l < L; ++l) {
+        // this layer's matrices, as packed or as the fp16 copy
+        const void* W[6] = {ctx->wq[l], ctx->wk[l], ctx->wv[l], ctx->wo[l], ctx->w_gate_up[l], ctx->w_down[l]};
+        if (f16)
+            for (int m = 0; m < 6; ++m) W[m] = w16[m];
         {
             PrefillGemmArgs p{};
             GemmArgs& g = p.g;
@@ -1139,6 +1163,7 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
             a.out_op = ws.op_attn;
             a.n_rows = n; a.R = R; a.n_heads = c.n_heads; a.n_kv_heads = c.n_kv_heads; a.pos0 = pos0; a.t_max = c.max_seq;
             a.op_f16 = f16;
+            if (f16) a.convert = conversion(l + 1, l);
             if ((rc = launch_prefill_attn(ctx, a, st))) return rc;
         }
         {

@@ -14,7 +14,7 @@
 // that the cache a short prompt leaves behind equals the row-limited path's up to rounding order. Longer passes are
 // bound by the matrix cores, where the split doubles the work: they run on fp16 operands instead (one fp16 plane per
 // activation, 11 significant bits; the layer's bf16 weights converted to fp16, which represents them exactly down to
-// 2^-17, by prefill_convert_f16_kernel at the start of each layer; fp32 accumulation). Epilogues write exactly what
+// 2^-17, by the attention launch before their use; fp32 accumulation). Epilogues write exactly what
 // the decode kernels' epilogues write (rotated, scaled query fragments; keys and values into the cache; residual
 // stream, next operand in the pass's format, sum-of-squares partials; SwiGLU operand).
 #pragma once
@@ -524,26 +524,42 @@ struct ConvertArgs {
     size_t end[6];  // running total of 16-byte units after each matrix
 };
 
-__global__ __launch_bounds__(256) void prefill_convert_f16_kernel(ConvertArgs c) {
-    const size_t total = c.end[5];
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (size_t)gridDim.x * 256) {
-        const u32x4* sp = c.src[0];
-        u32x4* dp = c.dst[0];
-        size_t first = 0;
+// Part `part` of `parts` equal ones, by the NT threads of a workgroup. Eight loads of a thread are in flight at once: next
+// to the attention a CU holds one workgroup of it.
+template <int NT>
+__device__ __forceinline__ void convert_part(const ConvertArgs& c, unsigned part, unsigned parts) {
+    constexpr int U = 8;
+    const size_t total = c.end[5], per = (total + parts - 1) / parts;
+    const size_t hi = min(total, (part + 1) * per);
+    for (size_t i0 = part * per + threadIdx.x; i0 < hi; i0 += NT * U) {
+        u32x4 v[U];
+        u32x4* dp[U];
 #pragma unroll
-        for (int k = 1; k < 6; ++k)
-            if (i >= c.end[k - 1]) { sp = c.src[k]; dp = c.dst[k]; first = c.end[k - 1]; }
-        const size_t j = i - first;
-        const u32x4 v = __builtin_nontemporal_load(sp + j);
-        u32x4 o;
+        for (int u = 0; u < U; ++u) {
+            const size_t i = i0 + u * NT;
+            const u32x4* sp = c.src[0];
+            size_t first = 0;
+            dp[u] = c.dst[0];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const f16 a = (f16)__uint_as_float(v[e] << 16), b = (f16)__uint_as_float(v[e] & 0xffff0000u);
-            o[e] = (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+            for (int k = 1; k < 6; ++k)
+                if (i >= c.end[k - 1]) { sp = c.src[k]; dp[u] = c.dst[k]; first = c.end[k - 1]; }
+            dp[u] += i - first;
+            if (i < hi) v[u] = __builtin_nontemporal_load(sp + (i - first));
         }
-        dp[j] = o;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            u32x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f16 a = (f16)__uint_as_float(v[u][e] << 16), b = (f16)__uint_as_float(v[u][e] & 0xffff0000u);
+                o[e] = (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+            }
+            if (i0 + u * NT < hi) *dp[u] = o;
+        }
     }
 }
+
+__global__ __launch_bounds__(256) void prefill_convert_f16_kernel(ConvertArgs c) { convert_part<256>(c, blockIdx.x, gridDim.x); }
 
 // ---- causal attention over the cache for a chunk of rows ----------------------------------------------------------
 struct PrefillAttnArgs {
@@ -553,6 +569,12 @@ struct PrefillAttnArgs {
     void* out_op;        // operand of the output projection, R row groups
     int n_rows, R, n_heads, n_kv_heads, pos0, t_max;
     int op_f16;          // format of out_op, as PrefillGemmArgs::op_f16
+    // Rows of the grid that are attention's; in an fp16 pass the workgroups behind them convert the weights of the
+    // projections that follow: attention is bound by the matrix cores and LDS and often has fewer workgroups than there are
+    // CUs, the conversion by HBM. 8B shape, per layer, against a conversion launch of 137-145 us of its own: 46 us less at 1100
+    // rows behind 1900 (144 attention workgroups), 17 at 2048 rows, 9 at 700, equal at 4096 (512 workgroups, no CU free).
+    int q_blocks;
+    ConvertArgs convert;
 };
 
 constexpr int kPrefillAttnNT = 2, kPrefillAttnWaves = 4;
@@ -575,11 +597,16 @@ __device__ __forceinline__ int prefill_attn_min_limit(const int (&limit)[NT]) {
 template <int HD, int NT>
 __global__ __launch_bounds__(kPrefillAttnWaves * 64) void prefill_attn_kernel(PrefillAttnArgs a) {
     constexpr int KK = HD / 32, CT = HD / 16;
+    if ((int)blockIdx.y >= a.q_blocks) {
+        convert_part<kPrefillAttnWaves * 64>(a.convert, (blockIdx.y - a.q_blocks) * gridDim.x + blockIdx.x,
+                                             (gridDim.y - a.q_blocks) * gridDim.x);
+        return;
+    }
     const int kvh = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int G = a.n_heads / a.n_kv_heads, nQ = a.n_rows * G, n_qt = a.R * G;
     // workgroups are handed out in blockIdx order: the last queries (most keys) go first, so that the CUs that finish
     // early pick up the short ones
-    const int t0 = ((int)(gridDim.y - 1 - blockIdx.y) * kPrefillAttnWaves + wave) * NT;  // first query tile of this wavefront
+    const int t0 = ((a.q_blocks - 1 - (int)blockIdx.y) * kPrefillAttnWaves + wave) * NT;  // first query tile of this wavefront
     if (t0 * 16 >= nQ) return;
     const int m16 = lane & 15, q4 = lane >> 4;
 
@@ -662,12 +689,16 @@ __global__ __launch_bounds__(NW * 64) void prefill_attn_lds_kernel(PrefillAttnAr
     constexpr int NSTAGE = kPrefillAttnStages;
     static_assert(FRB % NW == 0 && (NSTAGE - 2) * PER <= 63, "loads per wavefront and block; vmcnt holds 6 bits");
     extern __shared__ u32x4 attn_lds[];  // [NSTAGE][FRB][64]
+    if ((int)blockIdx.y >= a.q_blocks) {
+        convert_part<NW * 64>(a.convert, (blockIdx.y - a.q_blocks) * gridDim.x + blockIdx.x, (gridDim.y - a.q_blocks) * gridDim.x);
+        return;
+    }
     const int kvh = blockIdx.x, lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int G = a.n_heads / a.n_kv_heads, nQ = a.n_rows * G, n_qt = a.R * G;
     // workgroups are handed out in blockIdx order: the last queries (most keys) go first, so that the CUs that finish
     // early pick up the short ones
-    const int t_wg = (int)(gridDim.y - 1 - blockIdx.y) * NW * NT;  // first query tile of the workgroup
+    const int t_wg = (a.q_blocks - 1 - (int)blockIdx.y) * NW * NT;  // first query tile of the workgroup
     if (t_wg * 16 >= nQ) return;
     const int t0 = t_wg + wave * NT;
     const int m16 = lane & 15, q4 = lane >> 4;
