@@ -89,8 +89,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const int32_t* tokens, const
 // over the grid): key fragment (u, kk): a lane's 16 bytes are eight consecutive features of one position, 32 bytes of the
 // fp32 rows; value fragment c: eight consecutive positions of one feature, so the wavefront's eight 4-byte accesses cover 64
 // contiguous bytes of 32 rows' sixteen features. One element per thread, with its 64-bit divisions and 2-byte accesses 16
-// bytes apart, took 22.5 us to read 4096 positions of an 8-head, 128-feature layer (50 MB) and 170 us to load 32768; FIXME
-// and FIXME us now.
+// bytes apart, took 22.5 us to read 4096 positions of an 8-head, 128-feature layer (50 MB) and 170 us to load 32768;
+// 15.2 and 78.5 us now.
 template <bool LOAD>
 __global__ __launch_bounds__(256) void kv_move_kernel(float* K, float* V, kv_t* Kc, kv_t* Vt, int pos0, int T, int nkv, int hd,
                                                       int t_max, int aligned) {

@@ -158,12 +158,13 @@ def test_draws_over_chunk_edges(V):
 
 # Prompt passes over every tile the projections choose from: row counts at the tiles' edges and remainders, below and above
 # the fp16 threshold (640). "cols" has the column counts of the 8B shape's q/k/v and gate/up projections over a short
-# contraction, "rows" those of its residual projections (K-split and direct), "odd" an odd number of k-steps everywhere.
+# contraction, "rows" those of its residual projections (K-split and direct), "odd" an odd number of k-steps everywhere,
+# "one k-step" the shortest contraction there is.
 # Reference: the row-limited path on the same tokens, itself held to the oracle elsewhere; the two differ by rounding (fp16
 # keys and values, fp16 activations from 640 rows on), the bound is the one every bf16-model result is held to, and a k-step
 # or a tile left out or taken twice moves its rows by more (one of at most 45 k-steps: 1/sqrt(45) = 15 %).
 @pytest.mark.parametrize("kind,d,heads,kv,hd,ffn", [("cols", 256, 32, 8, 128, 14336), ("rows", 4096, 2, 1, 128, 256),
-                                                     ("odd", 544, 6, 2, 64, 1440)])
+                                                     ("odd", 544, 6, 2, 64, 1440), ("one k-step", 32, 1, 1, 64, 32)])
 def test_prompt_passes_at_the_edges_of_their_tiles(kind, d, heads, kv, hd, ffn):
     import paper_2505_24196_amd as clasp
     shape = si.ModelShape("edge-bf16", 3, d, heads, kv, hd, ffn, 2064, "bf16")
