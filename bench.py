@@ -22,8 +22,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # HBM bytes per launch of the dominant kernel from rocprofv3 PMC runs (FETCH_SIZE + WRITE_SIZE, each scaled by what the
 # counter reads for a 1 GiB copy); see profiles/gate_up_gemm_llama3-8b-shape_hbm_traffic.md. The projection runs as two
-# kernels (up to 8 rows: 236.0 + 1.84 MB, above: 236.8 + 1.84 MB); a step of the default workload launches them 128 : 15.
-MEASURED_TRAFFIC = {"llama3-8b-shape": (128 * (236.0e6 + 1.84e6) + 15 * (236.8e6 + 1.84e6)) / 143}
+# kernels (up to 8 rows: 235.8 + 0.3 MB, above: 236.8 + 1.28 MB); a step of the default workload launches them 128 : 15.
+MEASURED_TRAFFIC = {"llama3-8b-shape": (128 * (235.8e6 + 0.3e6) + 15 * (236.8e6 + 1.28e6)) / 143}
 
 WORKLOADS = {
     # benchmark configuration 2: the one the metric is quoted on
