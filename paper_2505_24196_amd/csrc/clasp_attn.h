@@ -529,6 +529,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(ATTN_F32_LEAD_PARAMS, Att
         sc[t] = p;
         den += p;
     }
+    // The last piece of four positions below pos0 reads weights up to pos0 + 2, of which those from n_keys > pos0 on belong
+    // to nobody: their values count as zero, but zero times a word that an earlier kernel left could be a NaN. (The barriers
+    // of block_sum stand between these stores and the reads.)
+    if (tid < 2) sc[n_keys + tid] = 0.f;
     den = block_sum(den, red + 4);
     // feature e of the output: sixteen lanes take positions l16*4 + 64*j .. +3 each, and own values l16, l16 + 16
     auto pv4 = [&](const f32x4& v, int t) {

@@ -7,7 +7,7 @@ import torch
 
 import synth_inputs as si
 from oracle import clasp_oracle as oc
-from tests.test_gpu_parity import assert_close
+from tests.test_gpu_parity import assert_close, oracle_dp_following
 
 pytestmark = pytest.mark.gpu
 
@@ -91,6 +91,52 @@ def test_fp32_attention_at_the_edges_of_its_pieces(heads, kv, hd, T):
     rk, rv = eng.clasp_kv_read(0, T, n)
     assert_close(rk.cpu().numpy().reshape(n, -1), k.reshape(n, -1).numpy(), 2e-5, "keys")
     assert_close(rv.cpu().numpy().reshape(n, -1), v.reshape(n, -1).numpy(), 2e-5, "values")
+    eng.close()
+
+
+# The last piece of four values that the fp32 attention takes reaches up to three positions beyond the prefix, where the
+# values count as zero: a weight multiplied with them has to be a number, also where the launch has no key of its own for it
+# (one row behind a prefix of T % 4 = 1 or 2, two rows at 1: plain decoding, drafts, candidates of the search). Every word of
+# LDS is a NaN before each call, so a weight that the kernel has not written shows. At the long prefixes those words lie
+# beyond what the projections of the same call use of LDS. Error bound as in the test above: the sum of 5000 softmax weights
+# adds sqrt(5000) * 2^-24 = 4e-6 of its size.
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 61, 62, 63, 5001, 5002, 5003])
+def test_fp32_attention_depends_on_no_stale_lds(T):
+    from tests.lds_fill import load
+    fill = load()
+    nan = 0x7fc00000
+    shape = si.ModelShape("edge-f32-lds", 3, 256, 4, 2, 64, 64, 112, "f32")
+    eng, om = build(shape, max_seq=(T + 32) // 32 * 32 + 32)
+    K, V = si.gen_kv(shape, 9, shape.n_layers, T, "cpu")
+    for l in range(shape.n_layers):
+        eng.clasp_kv_load(l, K[l], V[l])
+    toks = [int(t) for t in si.gen_tokens(5, 2, shape.vocab)]
+    dtoks = torch.tensor(toks, dtype=torch.int32, device="cuda")
+
+    def prefix():
+        cache = oc.KVCache(shape, T + 2)
+        cache.load(K.numpy().astype(np.float64), V.numpy().astype(np.float64))
+        return cache
+
+    cache = prefix()
+    ref = [om.token(t, T + i, cache, want_states=True) for i, t in enumerate(toks)]
+    for n in (1, 2):
+        fill(nan)
+        out = eng.clasp_verify_forward(dtoks[:n], T, want_hidden=True, want_logits=True)
+        assert_close(out["hidden"].cpu().numpy(), np.stack([r[0] for r in ref[:n]], 1), 2e-5, f"{n} rows: hidden")
+        assert_close(out["logits"].cpu().numpy(), np.stack([r[1] for r in ref[:n]]), 2e-5, f"{n} rows: logits")
+    logits, nxt = torch.zeros(shape.vocab, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    fill(nan)
+    eng.clasp_draft_sample([0, 1, 0], dtoks[:1], T, 1.0, torch.full((1,), 0.5, device="cuda"), logits, nxt)
+    assert_close(logits.cpu().numpy(), om.token(toks[0], T, prefix(), skip=np.array([0, 1, 0]))[1], 2e-5, "draft: logits")
+    X = torch.tensor(np.asarray(ref[0][0]), dtype=torch.float32, device="cuda")
+    fill(nan)
+    gpu = eng.clasp_dp_select(X, T, 2, want_tables=True)
+    dp = oracle_dp_following(om, X.cpu().numpy().astype(np.float64), T, prefix(), 2, gpu["choice"].cpu().numpy())
+    for k, key in enumerate(("sigma_c", "sigma_s")):
+        sc = gpu["scores"].cpu().numpy()[..., k]
+        assert np.array_equal(np.isnan(sc), np.isnan(dp[key])) and np.nanmax(np.abs(sc - dp[key])) <= 2e-5, key
+    assert_close(gpu["g_final"].cpu().numpy(), dp["g_final"], 2e-5, "g(L, M)")
     eng.close()
 
 
