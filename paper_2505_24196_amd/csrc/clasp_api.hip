@@ -45,6 +45,19 @@ void* static_scratch_ptr() {
     return g_scratch_ptr[dev];
 }
 
+// More than 64 KiB of LDS per workgroup has to be requested once per kernel and device. One of these per kernel.
+struct LdsOptIn {
+    uint64_t devices = 0;  // a bit each
+    template <class K>
+    bool request(int device, K kernel, size_t bytes) {
+        if (devices >> device & 1) return true;
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
+        devices |= 1ull << device;
+        return true;
+    }
+};
+static_assert(kMaxDevices == 64, "clasp_create refuses other devices (static_scratch_ptr)");
+
 // Tuning constants (each can be overridden on the compiler command line for sweeps; the values are the measured best
 // on MI355X at the LLaMA-3-8B and -70B shapes).
 // --- several-row streaming GEMM: a workgroup has CW x KW wavefronts (CW column-tile groups that share their activation
@@ -326,14 +339,9 @@ size_t gemv_lds_bytes(int K) {
 
 template <int EPI, int KWV, int ASRC = 0>
 int launch_gemv(const TimerScope& timer, const GemmArgs& g, size_t lds, hipStream_t st) {
-    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
+    static LdsOptIn opt_in;
     auto kernel = gemv_bf16_kernel<KWV, EPI, CLASP_GEMV_DEPTH, CLASP_ACT_SPLIT, ASRC>;
-    if (!opted_in) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemvMaxLds) !=
-            hipSuccess)
-            return CLASP_E_HIP;
-        opted_in = true;
-    }
+    if (!opt_in.request(timer.ctx->device, kernel, kGemvMaxLds)) return CLASP_E_HIP;
     launch_timed(timer, kernel, dim3(g.N / 16), dim3(KWV * 64), lds, st, GEMM_LEAD_ARGS(g), g, (g.K / 32 + KWV - 1) / KWV);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
@@ -344,13 +352,8 @@ int launch_gemv(const TimerScope& timer, const GemmArgs& g, size_t lds, hipStrea
 template <int EPI>
 int launch_few_rows(const clasp_ctx* ctx, const TimerScope& timer, const GemmArgs& g, hipStream_t st) {
     auto kernel = gemv_persistent_bf16_kernel<kResidentKSW, kResidentKW, EPI, CLASP_GEMVP_DEPTH, CLASP_ACT_SPLIT>;
-    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-    if (!opted_in) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * kFewRows) != hipSuccess)
-            return CLASP_E_HIP;
-        opted_in = true;
-    }
+    static LdsOptIn opt_in;
+    if (!opt_in.request(ctx->device, kernel, (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * kFewRows)) return CLASP_E_HIP;
     const int tiles = g.N / 16, rounds = (tiles + ctx->n_cu - 1) / ctx->n_cu, grid = (tiles + rounds - 1) / rounds;
     launch_timed(timer, kernel, dim3(grid), dim3((kResidentKW + 1) * 64),
                  (size_t)kResidentKW * kResidentKSW * CLASP_ACT_SPLIT * 64 * g.n_rows, st, GEMM_LEAD_ARGS(g), g);
@@ -461,15 +464,10 @@ int launch_gemm(const clasp_ctx* ctx, const GemmArgs& g, hipStream_t st, int kin
 }
 
 template <int HD, int NT, int NW, bool STREAM>
-int launch_attn_one(const AttnArgs& a, dim3 grid, hipStream_t st) {
+int launch_attn_one(const clasp_ctx* ctx, const AttnArgs& a, dim3 grid, hipStream_t st) {
     constexpr size_t lds = (size_t)NW * HD * 17 * sizeof(float);
-    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-    if (!opted_in) {
-        if (hipFuncSetAttribute((const void*)attn_bf16_kernel<HD, NT, NW, STREAM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds) != hipSuccess)
-            return CLASP_E_HIP;
-        opted_in = true;
-    }
+    static LdsOptIn opt_in;
+    if (!opt_in.request(ctx->device, attn_bf16_kernel<HD, NT, NW, STREAM>, lds)) return CLASP_E_HIP;
     hipLaunchKernelGGL((attn_bf16_kernel<HD, NT, NW, STREAM>), grid, dim3(NW * 64), lds, st, ATTN_LEAD_ARGS(a), a);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
@@ -477,18 +475,18 @@ int launch_attn_one(const AttnArgs& a, dim3 grid, hipStream_t st) {
 
 // short = latency-oriented launch: one query tile per workgroup, keys and values through plain (cached) loads
 template <int HD>
-int launch_attn_bf16(const AttnArgs& a, bool short_prefix, int nt, dim3 grid, hipStream_t st) {
-    if (short_prefix) return launch_attn_one<HD, 1, CLASP_ATTN_SHORT_WAVES, false>(a, grid, st);
-    if (nt == 1) return launch_attn_one<HD, 1, 8, true>(a, grid, st);
-    if (nt == 2) return launch_attn_one<HD, 2, 8, true>(a, grid, st);
+int launch_attn_bf16(const clasp_ctx* ctx, const AttnArgs& a, bool short_prefix, int nt, dim3 grid, hipStream_t st) {
+    if (short_prefix) return launch_attn_one<HD, 1, CLASP_ATTN_SHORT_WAVES, false>(ctx, a, grid, st);
+    if (nt == 1) return launch_attn_one<HD, 1, 8, true>(ctx, a, grid, st);
+    if (nt == 2) return launch_attn_one<HD, 2, 8, true>(ctx, a, grid, st);
     if constexpr (HD <= 64) {
-        if (nt == 3) return launch_attn_one<HD, 3, 8, true>(a, grid, st);
-        return launch_attn_one<HD, 4, 8, true>(a, grid, st);
+        if (nt == 3) return launch_attn_one<HD, 3, 8, true>(ctx, a, grid, st);
+        return launch_attn_one<HD, 4, 8, true>(ctx, a, grid, st);
     } else {
         // head_dim 128: three or four query tiles (33..64 queries of a KV group: 9..16 DP rows at 4 heads per group) need
         // more registers than two wavefronts per SIMD leave: four wavefronts, one per SIMD, each with the whole file
-        if (nt == 3) return launch_attn_one<HD, 3, 4, true>(a, grid, st);
-        return launch_attn_one<HD, 4, 4, true>(a, grid, st);
+        if (nt == 3) return launch_attn_one<HD, 3, 4, true>(ctx, a, grid, st);
+        return launch_attn_one<HD, 4, 4, true>(ctx, a, grid, st);
     }
 }
 
@@ -526,15 +524,10 @@ int launch_attention(const clasp_ctx* ctx, int layer, int n, int R, int mode, in
     if (c.dtype == CLASP_F32) {
         const size_t lds = attn_f32_lds_floats(c.head_dim, pos0, mode ? n : 1) * sizeof(float);
         auto kernel = c.head_dim % 8 == 0 ? attn_f32_kernel<true> : attn_f32_kernel<false>;
-        static bool opted_in[2] = {false, false};  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
-        bool& opted = opted_in[c.head_dim % 8 == 0];
-        if (!opted) {
-            constexpr size_t most = attn_f32_lds_floats(256, 8192, kMaxRows) * sizeof(float);  // check_config's limits
-            static_assert(most <= 160 * 1024, "LDS of a CU");
-            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most) != hipSuccess)
-                return CLASP_E_HIP;
-            opted = true;
-        }
+        static LdsOptIn opt_in[2];
+        constexpr size_t most = attn_f32_lds_floats(256, 8192, kMaxRows) * sizeof(float);  // check_config's limits
+        static_assert(most <= 160 * 1024, "LDS of a CU");
+        if (!opt_in[c.head_dim % 8 == 0].request(ctx->device, kernel, most)) return CLASP_E_HIP;
         hipLaunchKernelGGL(kernel, dim3(c.n_heads, n), dim3(256), lds, st, ATTN_F32_LEAD_ARGS(a), a);
         CLASP_LAUNCH_CHECK();
         return CLASP_OK;
@@ -572,8 +565,8 @@ int launch_attention(const clasp_ctx* ctx, int layer, int n, int R, int mode, in
     if (deferred_splits) split = deferred_splits;
     a.n_split = split;
     const dim3 grid(c.n_kv_heads, qgroups, split);
-    const int rc = c.head_dim == 64 ? launch_attn_bf16<64>(a, short_prefix, nt, grid, st)
-                                    : launch_attn_bf16<128>(a, short_prefix, nt, grid, st);
+    const int rc = c.head_dim == 64 ? launch_attn_bf16<64>(ctx, a, short_prefix, nt, grid, st)
+                                    : launch_attn_bf16<128>(ctx, a, short_prefix, nt, grid, st);
     if (rc) return rc;
     if (split > 1 && !deferred_splits) {
         hipLaunchKernelGGL(attn_combine_kernel, dim3(c.n_kv_heads, nQ), dim3(kCombineWaves * 64), 0, st, a, nt, qgroups);
@@ -964,25 +957,21 @@ RingPick pick_ring(RingTiles<T...>, int split, int R, int n_tiles, int ks, int n
 }
 
 template <int EPI, bool F16, class T>
-int launch_ring(const PrefillGemmArgs& p, int split, hipStream_t st) {
-    static bool opted_in = false;  // more than 64 KiB of LDS per workgroup has to be requested once per kernel
+int launch_ring(const clasp_ctx* ctx, const PrefillGemmArgs& p, int split, hipStream_t st) {
+    static LdsOptIn opt_in;
     auto kernel = prefill_ring_kernel<EPI, F16, T::WM, T::WN, T::RM, T::RN, T::STAGES, 2>;
     constexpr size_t lds = (size_t)T::STAGES * prefill_ring_frags<F16, T::WM, T::WN, T::RM, T::RN>() * 1024;
     static_assert(lds <= 160 * 1024, "LDS of a CU");
-    if (!opted_in) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-            return CLASP_E_HIP;
-        opted_in = true;
-    }
+    if (!opt_in.request(ctx->device, kernel, lds)) return CLASP_E_HIP;
     const int total = ((p.g.R + T::rows - 1) / T::rows) * ((p.g.N / 16 + T::cols - 1) / T::cols);
     hipLaunchKernelGGL(kernel, dim3((total + 7) / 8 * 8, split), dim3(T::WM * T::WN * 64), lds, st, p);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }
 template <int EPI, bool F16, class... T>
-int launch_picked(RingTiles<T...>, const RingPick& pick, const PrefillGemmArgs& p, hipStream_t st) {
+int launch_picked(const clasp_ctx* ctx, RingTiles<T...>, const RingPick& pick, const PrefillGemmArgs& p, hipStream_t st) {
     int index = 0, rc = CLASP_E_UNSUPPORTED;
-    ((index++ == pick.tile ? (void)(rc = launch_ring<EPI, F16, T>(p, pick.split, st)) : (void)0), ...);
+    ((index++ == pick.tile ? (void)(rc = launch_ring<EPI, F16, T>(ctx, p, pick.split, st)) : (void)0), ...);
     return rc;
 }
 
@@ -1009,7 +998,7 @@ int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStrea
             PrefillGemmArgs q = p;
             q.slab = (size_t)n * p.g.ldo;
             q.g.out = parts;
-            if ((rc = launch_picked<kEpiPartial, F16>(ring_tiles<kEpiPartial, F16>(), best, q, st))) return rc;
+            if ((rc = launch_picked<kEpiPartial, F16>(ctx, ring_tiles<kEpiPartial, F16>(), best, q, st))) return rc;
             q.g.out = p.g.out;
             static_assert(kPrefillMaxSplit == 4, "the cases below");
             auto reduce = best.split == 1 ? prefill_reduce_kernel<1, F16> : best.split == 2 ? prefill_reduce_kernel<2, F16>
@@ -1020,7 +1009,7 @@ int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStrea
             return CLASP_OK;
         }
         if constexpr (F16) {
-            if ((rc = launch_picked<kEpiResid, F16>(ring_tiles<kEpiResid, F16>(), direct, p, st))) return rc;
+            if ((rc = launch_picked<kEpiResid, F16>(ctx, ring_tiles<kEpiResid, F16>(), direct, p, st))) return rc;
             hipLaunchKernelGGL(prefill_rstd_kernel, dim3((n + 63) / 64), dim3(64, 16), 0, st, p.g.next_ss, n_tiles, p.ld_ss, n,
                                p.inv_dim, p.eps, p.next_rstd);
             CLASP_LAUNCH_CHECK();
@@ -1028,7 +1017,8 @@ int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStrea
         }
         return CLASP_E_UNSUPPORTED;  // not reached: the slices of a bf16 pass always fit
     } else {
-        return launch_picked<EPI, F16>(ring_tiles<EPI, F16>(), pick_ring(ring_tiles<EPI, F16>(), 1, R, n_tiles, ks, ctx->n_cu, 0.f), p, st);
+        const RingPick pick = pick_ring(ring_tiles<EPI, F16>(), 1, R, n_tiles, ks, ctx->n_cu, 0.f);
+        return launch_picked<EPI, F16>(ctx, ring_tiles<EPI, F16>(), pick, p, st);
     }
 }
 
@@ -1053,19 +1043,15 @@ int launch_prefill_attn(const clasp_ctx* ctx, PrefillAttnArgs a, hipStream_t st)
         constexpr int NW = CLASP_PREFILL_ATTN_LDS_WAVES ? CLASP_PREFILL_ATTN_LDS_WAVES : 4;
         a.q_blocks = (n_qt + NW * kPrefillAttnNT - 1) / (NW * kPrefillAttnNT);
         const dim3 grid(c.n_kv_heads, a.q_blocks + convert_rows);
-        static bool opted_in[2] = {false, false};
-        auto launch = [&](auto kernel, size_t lds, bool& opted) -> int {
-            if (!opted) {
-                if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-                    return CLASP_E_HIP;
-                opted = true;
-            }
+        static LdsOptIn opt_in[2];
+        auto launch = [&](auto kernel, size_t lds, LdsOptIn& opt) -> int {
+            if (!opt.request(ctx->device, kernel, lds)) return CLASP_E_HIP;
             hipLaunchKernelGGL(kernel, grid, dim3(NW * 64), lds, st, a);
             CLASP_LAUNCH_CHECK();
             return CLASP_OK;
         };
-        if (c.head_dim == 64) return launch(prefill_attn_lds_kernel<64, NW>, (size_t)kPrefillAttnStages * 8 * 1024, opted_in[0]);
-        return launch(prefill_attn_lds_kernel<128, NW>, (size_t)kPrefillAttnStages * 16 * 1024, opted_in[1]);
+        if (c.head_dim == 64) return launch(prefill_attn_lds_kernel<64, NW>, (size_t)kPrefillAttnStages * 8 * 1024, opt_in[0]);
+        return launch(prefill_attn_lds_kernel<128, NW>, (size_t)kPrefillAttnStages * 16 * 1024, opt_in[1]);
     }
     // two query tiles per wavefront share its key and value reads, one makes twice the workgroups: one until two cover the CUs
     auto launch = [&](auto kernel, int nt) -> int {

@@ -1,0 +1,52 @@
+"""What the library's host side launches, looked at without a GPU (launch_recorder.py)."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+F32, BF16 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("recorder") / "libhip_recorder.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-o", so, os.path.join(HERE, "hip_recorder.cpp")], check=True)
+    return so
+
+
+def record(recorder, jobs, library=None):
+    from paper_2505_24196_amd import binding
+    res = subprocess.run([sys.executable, os.path.join(HERE, "launch_recorder.py"), recorder, library or binding.LIB_PATH],
+                         input=json.dumps(jobs), capture_output=True, text=True, timeout=60)
+    assert res.returncode == 0, res.stderr
+    return json.loads(res.stdout)
+
+
+def config(L, d, heads, kv, hd, ffn, vocab, max_seq, max_rows, dtype):
+    return [L, d, heads, kv, hd, ffn, vocab, max_seq, max_rows, dtype]
+
+
+def test_large_lds_is_requested_on_every_device_of_the_process(recorder):
+    """A kernel may use more than 64 KiB of LDS only on the devices on which that was asked for: contexts of one process on
+    two devices, every family of kernels that goes beyond it."""
+    calls = {
+        tuple(config(2, 512, 2, 1, 256, 512, 1040, 8192, 32, F32)): [["verify", 32, 8100], ["dp", 8000, 2]],
+        tuple(config(2, 4096, 32, 8, 128, 14336, 16400, 2112, 32, BF16)): [["draft", 100], ["verify", 1, 2000], ["verify", 5, 64],
+                                                                           ["verify", 8, 2000], ["prefill", 300, 0, 384],
+                                                                           ["prefill", 1100, 900, 1152], ["prefill", 2048, 0, 2048]],
+        tuple(config(2, 512, 8, 2, 64, 1408, 16400, 2112, 32, BF16)): [["verify", 8, 2000], ["prefill", 1100, 900, 1152]],
+    }
+    jobs = [{"config": list(c), "device": dev, "calls": k} for dev in (0, 1) for c, k in calls.items()]
+    large = {0: set(), 1: set()}
+    for done in record(recorder, jobs)["calls"]:
+        assert done["rc"] == 0 and done["launches"], done["call"]
+        for l in done["launches"]:
+            assert l["lds"] <= 160 * 1024
+            assert l["lds_allowed"], (done["call"], l)
+            if l["lds"] > 64 * 1024:
+                large[l["device"]].add(l["kernel"].split("<")[0].split("::")[-1])
+    assert large[0] == large[1] == {"gemv_persistent_bf16_kernel", "attn_bf16_kernel", "attn_f32_kernel", "prefill_ring_kernel",
+                                    "prefill_attn_lds_kernel"}
