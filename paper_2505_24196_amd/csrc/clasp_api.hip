@@ -865,7 +865,13 @@ struct PrefillWs {
 };
 
 bool prefill_uses_f16(int rows) { return CLASP_PREFILL_F16_ROWS > 0 && rows >= CLASP_PREFILL_F16_ROWS; }
-constexpr int kPrefillSplitRows = 1024, kPrefillMaxSplit = 4;  // K-split: most slices, room for that many of this many rows
+constexpr int kPrefillMaxSplit = 4;  // slices a contraction is cut into at most
+// Rows of slices that the workspace of a pass of `chunk` rows holds: four slices of up to 1024 rows, and one of the longest
+// bf16 pass, whose residual projections always take that way.
+size_t prefill_part_rows(int chunk) {
+    const int longest_bf16 = CLASP_PREFILL_F16_ROWS > 0 ? std::min(chunk, CLASP_PREFILL_F16_ROWS - 1) : chunk;
+    return std::max(kPrefillMaxSplit * std::min(chunk, 1024), longest_bf16);
+}
 
 size_t carve_prefill(const clasp_config& c, int chunk, char* base, PrefillWs* ws) {
     Carver w{base};
@@ -882,7 +888,7 @@ size_t carve_prefill(const clasp_config& c, int chunk, char* base, PrefillWs* ws
     t.op_attn = w.take<void>(C * qd * 4);
     t.op_act = w.take<void>(C * (size_t)c.d_ffn * 4);
     t.q_frag = w.take<void>(C * qd * 2);
-    t.parts = w.take<float>((size_t)kPrefillMaxSplit * std::min<size_t>(C, kPrefillSplitRows) * d * 4);
+    t.parts = w.take<float>(prefill_part_rows(chunk) * d * 4);
     const size_t kvd = (size_t)c.n_kv_heads * c.head_dim;
     t.w16 = prefill_uses_f16(chunk) ? w.take<char>((2 * qd * d + 2 * kvd * d + 3 * d * (size_t)c.d_ffn) * 2) : nullptr;
     if (ws) *ws = t;
@@ -978,8 +984,8 @@ int launch_picked(const clasp_ctx* ctx, RingTiles<T...>, const RingPick& pick, c
 // One projection. F16: the pass runs on fp16 operands (p.g.A is an fp16 plane, p.g.W an fp16 copy of the weights). The
 // residual projections (N = d_model, too few columns for the CUs below some 4000 rows) may split the contraction over
 // workgroups: the slices go to `parts` (room for part_rows rows) and prefill_reduce_kernel finishes them; without a split
-// the epilogue runs in the GEMM and prefill_rstd_kernel adds up its sums of squares. bf16 passes are short enough to
-// always take the first way, fp16 passes take the cheaper one.
+// the epilogue runs in the GEMM and prefill_rstd_kernel adds up its sums of squares. bf16 passes, whose slices always fit,
+// take the first way, fp16 passes the cheaper one.
 template <int EPI, bool F16>
 int launch_prefill_gemm(const clasp_ctx* ctx, const PrefillGemmArgs& p, hipStream_t st, float* parts = nullptr,
                         size_t part_rows = 0) {
@@ -1082,7 +1088,7 @@ int prefill_chunk(const clasp_ctx* ctx, const PrefillWs& ws, int ld, const int32
                            c.vocab, d, n, ws.h, ws.op_h, R, ctx->attn_norm[0], ws.rstd_h, c.rms_eps);
         CLASP_LAUNCH_CHECK();
     }
-    const size_t part_rows = (size_t)kPrefillMaxSplit * std::min(ld, kPrefillSplitRows);
+    const size_t part_rows = prefill_part_rows(ld);
     auto gemm = [&](auto epi, const PrefillGemmArgs& p, float* parts) -> int {
         constexpr int EPI = decltype(epi)::value;
         return f16 ? launch_prefill_gemm<EPI, true>(ctx, p, st, parts, part_rows)

@@ -33,6 +33,7 @@ int record(const void* f, Dim3 g, Dim3 b, size_t lds) {
 }  // namespace
 
 extern "C" {
+char __hip_fatbin[1];  // for a library compiled for the host alone: there is no device code to point at
 void recorder_set_device(int dev) { g_device = dev; }
 void recorder_clear() { g_log.clear(); }
 // One line per launch: kernel, grid x, y, z, threads, dynamic LDS bytes, device, whether that much LDS was asked for there.

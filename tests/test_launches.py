@@ -50,3 +50,20 @@ def test_large_lds_is_requested_on_every_device_of_the_process(recorder):
                 large[l["device"]].add(l["kernel"].split("<")[0].split("::")[-1])
     assert large[0] == large[1] == {"gemv_persistent_bf16_kernel", "attn_bf16_kernel", "attn_f32_kernel", "prefill_ring_kernel",
                                     "prefill_attn_lds_kernel"}
+
+
+def test_prompt_passes_with_the_fp16_form_turned_off(recorder, tmp_path):
+    """CLASP_PREFILL_F16_ROWS = 0 (a build-time option: no pass takes fp16 operands): the bf16 form of a pass always leaves the
+    sums of its residual projections in the workspace, which has to hold them at every number of rows a pass may have."""
+    from paper_2505_24196_amd import build
+    so = str(tmp_path / "libclasp_host.so")
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "--offload-host-only", "-fuse-cuid=none", "-O1", "-std=c++17", "-shared", "-fPIC",
+                    "-Wno-unused-command-line-argument", "-DCLASP_PREFILL_F16_ROWS=0", "-o", so] + build.SOURCES, check=True)
+    rows = [(128, 128), (640, 640), (1100, 1152), (4096, 4096), (4097, 4224), (8192, 8192)]
+    calls = [["prefill", n, 0, chunk] for n, chunk in rows]
+    for done in record(recorder, [{"config": config(2, 4096, 32, 8, 128, 14336, 16400, 8192, 16, BF16), "calls": calls}], so)["calls"]:
+        assert done["rc"] == 0, done["call"]
+        assert not any("true" in l["kernel"] for l in done["launches"] if "prefill_ring" in l["kernel"])
+        for l in done["launches"]:  # kEpiPartial: slices (grid y) of `rows` rows each
+            if "prefill_ring_kernel<4," in l["kernel"]:
+                assert l["grid"][1] * done["call"][1] <= max(4 * min(done["call"][3], 1024), done["call"][3])
