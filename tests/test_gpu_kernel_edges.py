@@ -202,26 +202,41 @@ def test_draws_over_chunk_edges(V):
     eng.close()
 
 
-# Prompt passes over every tile the projections choose from: row counts at the tiles' edges and remainders, below and above
-# the fp16 threshold (640). "cols" has the column counts of the 8B shape's q/k/v and gate/up projections over a short
-# contraction, "rows" those of its residual projections (K-split and direct), "odd" an odd number of k-steps everywhere,
-# "one k-step" the shortest contraction there is.
+# Prompt passes over every tile, K-split and attention form the launches choose from (tests/test_launches.py holds the shapes and
+# row counts below to that, on 256 CUs): row counts at the tiles' edges and remainders, below and above the fp16 threshold
+# (640). "cols" has the column counts of the 8B shape's q/k/v and gate/up projections over a short contraction, "rows" those
+# of its residual projections over a short one, "odd" an odd number of k-steps everywhere, "one k-step" the shortest
+# contraction there is; "wide" is the 8B width itself, whose long contractions take the larger tiles of the residual
+# projections in slices, "heads" enough query heads for two tiles per wavefront in the short-prompt attention.
 # Reference: the row-limited path on the same tokens, itself held to the oracle elsewhere; the two differ by rounding (fp16
 # keys and values, fp16 activations from 640 rows on), the bound is the one every bf16-model result is held to, and a k-step
-# or a tile left out or taken twice moves its rows by more (one of at most 45 k-steps: 1/sqrt(45) = 15 %).
-@pytest.mark.parametrize("kind,d,heads,kv,hd,ffn", [("cols", 256, 32, 8, 128, 14336), ("rows", 4096, 2, 1, 128, 256),
-                                                     ("odd", 544, 6, 2, 64, 1440), ("one k-step", 32, 1, 1, 64, 32)])
-def test_prompt_passes_at_the_edges_of_their_tiles(kind, d, heads, kv, hd, ffn):
+# or a tile left out or taken twice moves its rows by more (one k-step of the longest contractions, 448: 1/sqrt(448) = 4.7 %).
+PROMPT_ROWS = (1, 16, 33, 64, 65, 97, 128, 129, 160, 161, 256, 257, 300, 321, 448, 449, 600, 639, 640, 641, 700, 833, 1000, 1100,
+               1537, 2049)
+PROMPT_PASSES = {  # kind: (d, heads, kv, hd, ffn), row counts
+    "cols": ((256, 32, 8, 128, 14336), PROMPT_ROWS),
+    "rows": ((4096, 2, 1, 128, 256), PROMPT_ROWS),
+    "odd": ((544, 6, 2, 64, 1440), PROMPT_ROWS),
+    "one k-step": ((32, 1, 1, 64, 32), PROMPT_ROWS),
+    "wide": ((4096, 32, 8, 128, 14336), (350, 400, 600, 639, 700, 900, 1100, 2048, 3500, 4096)),
+    "heads": ((256, 64, 8, 128, 64), (500, 600, 640, 991)),
+    "heads 64": ((256, 64, 8, 64, 64), (500, 600, 640, 991)),
+}
+
+
+@pytest.mark.parametrize("kind", PROMPT_PASSES)
+def test_prompt_passes_at_the_edges_of_their_tiles(kind):
     import paper_2505_24196_amd as clasp
+    (d, heads, kv, hd, ffn), rows = PROMPT_PASSES[kind]
+    most = max(rows) + 51
     shape = si.ModelShape("edge-bf16", 3, d, heads, kv, hd, ffn, 2064, "bf16")
     model = si.gen_model(shape, 3, "cuda")
-    ref, eng = (clasp.Engine(shape, max_seq=2112, max_rows=32).load(model) for _ in range(2))
-    toks = si.gen_tokens(5, 2100, shape.vocab).cuda()
-    for s in range(0, 2100, 30):
+    ref, eng = (clasp.Engine(shape, max_seq=(most + 31) // 32 * 32, max_rows=32).load(model) for _ in range(2))
+    toks = si.gen_tokens(5, most, shape.vocab).cuda()
+    for s in range(0, most, 30):
         ref.clasp_verify_forward(toks[s:s + 30], s)
-    want = [[t.clone() for t in ref.clasp_kv_read(l, 0, 2100)] for l in range(3)]
-    for n in (1, 16, 33, 64, 65, 97, 128, 129, 160, 161, 256, 257, 300, 321, 448, 449, 600, 639, 640, 641, 700, 833, 1000, 1100,
-              1537, 2049):
+    want = [[t.clone() for t in ref.clasp_kv_read(l, 0, most)] for l in range(3)]
+    for n in rows:
         eng.clasp_prefill(toks[:n], 0, (n + 127) // 128 * 128)
         for l in range(3):
             for got, full in zip(eng.clasp_kv_read(l, 0, n), want[l]):

@@ -67,3 +67,18 @@ def test_prompt_passes_with_the_fp16_form_turned_off(recorder, tmp_path):
         for l in done["launches"]:  # kEpiPartial: slices (grid y) of `rows` rows each
             if "prefill_ring_kernel<4," in l["kernel"]:
                 assert l["grid"][1] * done["call"][1] <= max(4 * min(done["call"][3], 1024), done["call"][3])
+
+
+def test_prompt_pass_tests_reach_every_kernel_of_the_prompt_pass(recorder):
+    """The GPU test of the prompt passes claims every tile, K-split and attention form: the kernels its shapes and row counts
+    launch on 256 CUs are all the ones that are compiled."""
+    from tests.test_gpu_kernel_edges import PROMPT_PASSES
+    jobs = [{"config": config(3, *shape, 2064, 4224, 32, BF16),
+             "calls": [["prefill", n, 0, (n + 127) // 128 * 128] for n in rows]} for shape, rows in PROMPT_PASSES.values()]
+    out = record(recorder, jobs)
+    assert all(done["rc"] == 0 for done in out["calls"])
+    launches = [l for done in out["calls"] for l in done["launches"]]
+    compiled = {k for k in out["kernels"] if "clasp::prefill_" in k}
+    assert len(compiled) > 40 and compiled == {l["kernel"] for l in launches if "clasp::prefill_" in l["kernel"]}
+    splits = {(f16, l["grid"][1]) for l in launches for f16 in ("false", "true") if f"prefill_ring_kernel<4, {f16}," in l["kernel"]}
+    assert splits == {(f16, s) for f16 in ("false", "true") for s in (1, 2, 3, 4)}
