@@ -832,19 +832,17 @@ SampleArgs sample_args(const clasp_ctx* ctx, float temperature) {
 }
 
 int launch_draw(const SampleArgs& a, hipStream_t st) {
-    if (a.V <= kSmallVocab) {
-        hipLaunchKernelGGL(draw_kernel<true>, dim3(1), dim3(kDrawThreads), 0, st, a);
+    const int mode = draw_mode(a.V, a.n), chunks = sample_cut(a.V).chunks;
+    if (mode != kDrawAll) {
+        hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 2 * a.n + 1), dim3(kSampleThreads), 0, st, a);
         CLASP_LAUNCH_CHECK();
-        return CLASP_OK;
     }
-    const int chunks = sample_cut(a.V).chunks;
-    hipLaunchKernelGGL(chunk_stats_kernel, dim3(chunks, 2 * a.n + 1), dim3(kSampleThreads), 0, st, a);
-    CLASP_LAUNCH_CHECK();
-    if (a.q) {
+    if (mode == kDrawChunks && a.q) {
         hipLaunchKernelGGL(residual_sums_kernel, dim3(chunks), dim3(kDrawThreads), 0, st, a);
         CLASP_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(draw_kernel<false>, dim3(1), dim3(kDrawThreads), 0, st, a);
+    auto draw = mode == kDrawAll ? draw_kernel<kDrawAll> : mode == kDrawRow ? draw_kernel<kDrawRow> : draw_kernel<kDrawChunks>;
+    hipLaunchKernelGGL(draw, dim3(1), dim3(kDrawThreads), 0, st, a);
     CLASP_LAUNCH_CHECK();
     return CLASP_OK;
 }

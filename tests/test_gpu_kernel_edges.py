@@ -140,11 +140,12 @@ def test_fp32_attention_depends_on_no_stale_lds(T):
     eng.close()
 
 
-# Draws and acceptance over rows cut into chunks: one chunk, a last chunk of 16 entries, 64 full chunks, chunks larger than
-# the entries kept in registers. The mass sits on at most eight tokens, several of them at chunk edges. A running sum of the
+# Draws and acceptance: in one launch (a draw up to 4096 entries, one to four a thread; acceptance up to 1024 entries and seven
+# drafts), in two (acceptance up to 4096) and over rows cut into chunks, the last of them of 16 entries, 64 full ones,
+# larger than what stays in registers. The mass sits on at most eight tokens, several of them at chunk edges. A running sum of the
 # others' weights (e^-39 each) is exact to 1e-7, of the eight and of their fp32 exponentials to 16 * 2^-23 + 8 * 2^-24 = 2.4e-6:
 # draws whose uniform number is further than 1e-4 from every float64 running sum have to agree.
-@pytest.mark.parametrize("V", [16, 1024, 1040, 2064, 65536, 128256, 262160])
+@pytest.mark.parametrize("V", [16, 512, 528, 1024, 1040, 2064, 4096, 4112, 8192, 8208, 65536, 128256, 262160])
 def test_draws_over_chunk_edges(V):
     import paper_2505_24196_amd as clasp
     shape = si.ModelShape("edge-vocab", 1, 32, 2, 1, 16, 32, V, "f32")
@@ -176,7 +177,7 @@ def test_draws_over_chunk_edges(V):
     eng.clasp_sample_token(dev(one_nan), 1.0, torch.tensor([0.5], device="cuda"), tok)
     assert int(tok) == -1
     # acceptance: n drafts, the first rejected one at every place (its draft has probability ~0 under the full model)
-    for n in (1, 5, 31):
+    for n in (1, 5, 7, 8, 31):
         for a in sorted({0, n // 2, n - 1, n}):
             p, q = base.repeat(n + 1, 1), base.repeat(n, 1)
             drafts = [hot[i % len(hot)] for i in range(n)]

@@ -82,3 +82,19 @@ def test_prompt_pass_tests_reach_every_kernel_of_the_prompt_pass(recorder):
     assert len(compiled) > 40 and compiled == {l["kernel"] for l in launches if "clasp::prefill_" in l["kernel"]}
     splits = {(f16, l["grid"][1]) for l in launches for f16 in ("false", "true") if f"prefill_ring_kernel<4, {f16}," in l["kernel"]}
     assert splits == {(f16, s) for f16 in ("false", "true") for s in (1, 2, 3, 4)}
+
+
+@pytest.mark.parametrize("V,n,kernels", [
+    (16, 7, ["draw_kernel<2>"]), (1024, 7, ["draw_kernel<2>"]),
+    (1024, 8, ["chunk_stats_kernel", "draw_kernel<1>"]), (1040, 1, ["chunk_stats_kernel", "draw_kernel<1>"]),
+    (4096, 31, ["chunk_stats_kernel", "draw_kernel<1>"]),
+    (4112, 1, ["chunk_stats_kernel", "residual_sums_kernel", "draw_kernel<0>"])])
+def test_launches_of_an_acceptance_round(recorder, V, n, kernels):
+    """One launch for few drafts over few entries, two while a workgroup holds a row in registers, three beyond; the draw of
+    clasp_draft_sample takes one launch up to 4096 entries and two beyond."""
+    done = record(recorder, [{"config": config(1, 64, 1, 1, 64, 64, V, 32, 32, BF16), "calls": [["accept", n], ["draft", 0]]}])["calls"]
+    names = [[l["kernel"].split("(")[0].split("::")[-1] for l in d["launches"]] for d in done]
+    assert [d["rc"] for d in done] == [0, 0]
+    assert names[0] == kernels
+    draw = ["draw_kernel<2>"] if V <= 4096 else ["chunk_stats_kernel", "draw_kernel<0>"]
+    assert names[1][-len(draw):] == draw
