@@ -807,10 +807,13 @@ int launch_kv_move(const clasp_ctx* ctx, int layer, int pos0, int n, float* K, f
     char *Kc = ctx->k_cache + (size_t)layer * ctx->kv_layer_bytes, *Vt = ctx->v_cache + (size_t)layer * ctx->kv_layer_bytes;
     if (c.dtype == CLASP_BF16) {
         const int aligned = (reinterpret_cast<uintptr_t>(K) & 15) == 0;  // the caller's rows: 16-byte pieces only if they are
-        hipLaunchKernelGGL(kv_move_kernel<LOAD>, dim3(2048), dim3(256), 0, st, K, V, reinterpret_cast<kv_t*>(Kc),
+        // a wavefront per fragment while there are few: 2048 workgroups whatever the size took 2.5 us for one position
+        const long long frags = (long long)((pos0 + n + 31) / 32 - pos0 / 32) * c.n_kv_heads * (c.head_dim / 8);
+        hipLaunchKernelGGL(kv_move_kernel<LOAD>, dim3((unsigned)std::min(2048ll, (frags + 3) / 4)), dim3(256), 0, st, K, V, reinterpret_cast<kv_t*>(Kc),
                            reinterpret_cast<kv_t*>(Vt), pos0, n, c.n_kv_heads, c.head_dim, c.max_seq, aligned);
     } else {
-        hipLaunchKernelGGL(kv_move_f32_kernel<LOAD>, dim3(1024), dim3(256), 0, st, K, V, reinterpret_cast<float*>(Kc),
+        const long long elems = (long long)n * c.n_kv_heads * c.head_dim;
+        hipLaunchKernelGGL(kv_move_f32_kernel<LOAD>, dim3((unsigned)std::min(1024ll, (elems + 255) / 256)), dim3(256), 0, st, K, V, reinterpret_cast<float*>(Kc),
                            reinterpret_cast<float*>(Vt), pos0, n, c.n_kv_heads, c.head_dim, c.max_seq);
     }
     CLASP_LAUNCH_CHECK();

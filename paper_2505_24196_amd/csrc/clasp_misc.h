@@ -150,11 +150,15 @@ __global__ __launch_bounds__(256) void kv_move_kernel(float* K, float* V, kv_t* 
                     for (int e = 0; e < 8; ++e) col[e * ld] = from_kv(x[e]);
                 }
             } else {  // a block at the range's end: positions outside it stay as they are
+                if constexpr (LOAD) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    if (t0 + e < 0 || t0 + e >= T) continue;
-                    if constexpr (LOAD) frag[e] = to_kv(col[e * ld]);
-                    else col[e * ld] = from_kv(frag[e]);
+                    for (int e = 0; e < 8; ++e)
+                        if (t0 + e >= 0 && t0 + e < T) frag[e] = to_kv(col[e * ld]);
+                } else {
+                    const kvx8 x = *reinterpret_cast<const kvx8*>(frag);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (t0 + e >= 0 && t0 + e < T) col[e * ld] = from_kv(x[e]);
                 }
             }
         }

@@ -31,6 +31,10 @@ def call(lib, ctx, cfg, name, *a):
         return lib.clasp_draft_sample(ctx, mask, p, a[0], f(1.0), p, p, p, None)
     if name == "accept":  # drafts
         return lib.clasp_spec_accept(ctx, p, p, C.c_size_t(cfg.vocab), p, a[0], f(1.0), p, p, p, p, None)
+    if name == "kv_load":  # positions
+        return lib.clasp_kv_load(ctx, 0, p, p, a[0], None)
+    if name == "kv_read":  # first position, positions
+        return lib.clasp_kv_read(ctx, 0, a[0], a[1], p, p, None)
     if name == "prefill":  # rows, position, rows per pass
         need = lib.clasp_prefill_workspace_bytes(C.byref(cfg), a[2])
         return lib.clasp_prefill(ctx, p, a[0], a[1], a[2], p, C.c_size_t(need), None)

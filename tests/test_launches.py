@@ -98,3 +98,13 @@ def test_launches_of_an_acceptance_round(recorder, V, n, kernels):
     assert names[0] == kernels
     draw = ["draw_kernel<2>"] if V <= 4096 else ["chunk_stats_kernel", "draw_kernel<0>"]
     assert names[1][-len(draw):] == draw
+
+
+def test_cache_moves_launch_what_they_move(recorder):
+    """bf16 models: four fragments of 1 KiB a workgroup (a block of 32 positions of one head is head_dim / 8 of them), up to 2048
+    workgroups; fp32 models: 256 elements, up to 1024."""
+    calls = [["kv_load", 1], ["kv_read", 31, 2], ["kv_read", 3, 29], ["kv_load", 4096]]
+    done = record(recorder, [{"config": config(1, 512, 8, 2, 64, 64, 112, 4096, 16, dtype), "calls": calls} for dtype in (BF16, F32)])["calls"]
+    assert all(d["rc"] == 0 and len(d["launches"]) == 1 for d in done)
+    grids = [d["launches"][0]["grid"][0] for d in done]
+    assert grids == [2 * 8 // 4, 2 * 2 * 8 // 4, 2 * 8 // 4, 128 * 2 * 8 // 4, 1, 1, 15, 1024]
