@@ -84,7 +84,7 @@ static_assert(kMaxDevices == 64, "clasp_create refuses other devices (static_scr
 #define CLASP_OPROJ_NACC 1
 #endif
 #ifndef CLASP_GATEUP_CW
-#define CLASP_GATEUP_CW 4  // gate|up and lm_head only take this kernel when they have no more tiles than the GPU has CUs
+#define CLASP_GATEUP_CW 4  // one row group of gate/up with more tiles than the GPU has CUs and K beyond 4096 (the 70B shape)
 #endif
 #ifndef CLASP_GATEUP_KW
 #define CLASP_GATEUP_KW 2
@@ -121,12 +121,13 @@ static_assert(kMaxDevices == 64, "clasp_create refuses other devices (static_scr
 #ifndef CLASP_DOWNP_NACC
 #define CLASP_DOWNP_NACC 2
 #endif
-// launches with two 16-row groups (17..32 rows): four activation loads per k-step, shared by this many column tiles
+// the DP's down projection with two 16-row groups (17..32 candidates): four activation loads per k-step, shared by this many
+// column tiles (the other launches of two row groups take theirs from the number of tiles, launch_gemm_bf16)
 #ifndef CLASP_R2_NACC
 #define CLASP_R2_NACC 4
 #endif
 #ifndef CLASP_R2_DEPTH
-#define CLASP_R2_DEPTH 2  // k-steps per register stage of those launches
+#define CLASP_R2_DEPTH 2  // k-steps per register stage of that launch
 #endif
 // k-steps per register stage (two stages in flight)
 #ifndef CLASP_STREAM_DEPTH
@@ -427,15 +428,17 @@ int launch_gemm_bf16(const clasp_ctx* ctx, const TimerScope& timer, const GemmAr
             using I4 = integral_constant<int, 4>;
             using I8 = integral_constant<int, 8>;
             if constexpr (EPI == kEpiResid) {
-                // projections onto d_model: two tiles from 2 x CUs tiles on (70B shape, 512 tiles: 7196 us per search with two,
-                // 7249 with one), one below (8B shape, 256 tiles, verify pass of 24 rows on six layers: 1160 us with one, 1219
-                // with two, 1265 with two and four, which also spilled registers)
+                // projections onto d_model: one tile below 2 x CUs tiles (8B shape, 256 tiles, verify pass of 24 rows on six
+                // layers: 1160 us with one, 1219 with two, 1265 with two and four, which also spilled registers). From there
+                // on two, as before: 70B shape, 512 tiles, 7196 us per search with two and 7249 with one, no more than two
+                // runs of the call differ by
                 if (tiles >= 2 * ctx->n_cu) launch_two(I2{}, I1{}, I8{}, I2{});
                 else launch_two(I1{}, I1{}, I8{}, I4{});
             } else if constexpr (EPI == kEpiSwiglu) {
-                // four wavefronts of four tiles when that makes a workgroup for three quarters of the CUs (70B shape, 224
-                // workgroups: 7250 us per search, 7294 with two), else two and twice the K slices (8B shape, 112 -> 224
-                // workgroups: 1145 -> 1032 us for the pass above)
+                // two wavefronts of four tiles and four K slices while four wavefronts and two slices make a workgroup for
+                // less than three quarters of the CUs (8B shape, 112 -> 224 workgroups: 1145 -> 1032 us for the pass above).
+                // From there on four, as before: 70B shape, 224 workgroups, 7250 us per search with four and 7294 with two,
+                // no more than two runs of the call differ by
                 if ((tiles + 15) / 16 * 4 >= 3 * ctx->n_cu) launch_two(I4{}, I4{}, I2{}, I2{});
                 else launch_two(I4{}, I2{}, I4{}, I2{});
             } else if constexpr (EPI == kEpiQkv) {
@@ -533,7 +536,7 @@ int launch_attention(const clasp_ctx* ctx, int layer, int n, int R, int mode, in
         return CLASP_OK;
     }
     // Short prefixes are latency-bound: one query tile per workgroup (more workgroups, each key block re-read from
-    // L2 by the few workgroups of a KV head) and 16 wavefronts, so that a wavefront sees one or two key blocks.
+    // L2 by the few workgroups of a KV head), whose wavefronts see a few key blocks each.
     // Long prefixes are bandwidth-bound: up to 4 query tiles per workgroup (keys read once) and the prefix split
     // across workgroups.
     const int nQ = n * ctx->group, ntq = (nQ + 15) / 16;
@@ -852,9 +855,12 @@ int launch_draw(const SampleArgs& a, hipStream_t st) {
 
 // ---- prompt processing with many rows per pass ---------------------------------------------------------------------
 constexpr int kPrefillMaxChunk = 8192;
-// Passes of at least this many rows (640: measured break-even at the 8B shape is between 512 and 640) run their GEMMs on fp16 MFMAs: one fp16 plane per activation instead of the bf16
-// hi / lo pair (half the matrix-core work) against an fp16 copy of the layer's weights made at the start of the layer
-// (one more read and write of the layer per pass, which shorter passes would not earn back). 0 = never.
+// Passes of at least this many rows run their GEMMs on fp16 MFMAs: one fp16 plane per activation instead of the bf16 hi / lo
+// pair (half the matrix-core work) against an fp16 copy of the weights, made behind the attention launches (one more read
+// and write of the layer per pass, which shorter passes do not earn back). 0 = never. fp16 against bf16 form of one pass,
+// in us: 8B width, six layers, 512 rows 2422 / 2348, 576 2648 / 2730, 640 2804 / 2751, 704 3080 / 3387, 1024 3373 / 4470; 70B width,
+// three layers, 448 rows 3305 / 3104, 512 3260 / 3279, 640 3724 / 3986. Models so small that launches bound them lose by it
+// at any size (d_model 512, six layers: 640 rows 437 / 294, 1024 rows 510 / 409).
 #ifndef CLASP_PREFILL_F16_ROWS
 #define CLASP_PREFILL_F16_ROWS 640
 #endif

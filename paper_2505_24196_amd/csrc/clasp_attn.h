@@ -14,7 +14,8 @@
 // fragment of O^T = V^T . P^T); V is cached transposed so that its fragments are 16-byte loads too. Wavefronts of a
 // workgroup take 32-key blocks round-robin and are merged through LDS in a fixed order; several workgroups may split
 // a long prefix (grid.z); attn_combine_kernel then merges their partial results in split order.
-// fp32 kernel: plain loops, rotary embedding applied in the kernel, exact softmax over all visible keys.
+// fp32 kernel: vector arithmetic, exact softmax over all visible keys; the projection leaves q, k and v un-rotated, the kernel
+// rotates them on their way into LDS.
 #pragma once
 #include "clasp_common.h"
 

@@ -19,8 +19,8 @@ constexpr int kDtF32 = 0, kDtBf16 = 1;
 // An activation matrix X[rows <= 16*R][K] that a GEMM will contract over K is kept in HBM per k-step s (32
 // consecutive k) and row group rg (16 rows) as two planes of 16 rows x 32 bf16, row-major: "hi" = round(x) and
 // "lo" = round(x - hi). MFMA lane (q*16 + r) fetches X[rg*16 + r][s*32 + q*8 .. +8] of each plane with one 16-byte
-// load and feeds it to v_mfma_f32_16x16x32_bf16 unchanged; lanes whose row does not exist fetch nothing, so the
-// traffic follows the number of live rows. hi + lo carries 16 mantissa bits: the activations lose next to nothing
+// load and feeds it to v_mfma_f32_16x16x32_bf16 unchanged; lanes whose row does not exist read the last live row's, so
+// the traffic follows the number of live rows. hi + lo carries 16 mantissa bits: the activations lose next to nothing
 // against fp32 while the weights stay bf16.
 __device__ __forceinline__ size_t frag_elem_offset(int R, int row, int k) {
     const int s = k >> 5, rg = row >> 4, r = row & 15;
@@ -176,12 +176,7 @@ __device__ __forceinline__ size_t frag16_elem_offset(int R, int row, int k) {
     return ((((size_t)s * R + rg) * 4 + q) * 16 + r) * 8 + (k & 7);
 }
 
-// Operand element in the format a prompt pass runs in: fp16 plane (f16 != 0) or the bf16 hi / lo planes.
-__device__ __forceinline__ void store_operand_fmt(void* buf, int R, int row, int k, float v, int f16_plane) {
-    if (f16_plane) reinterpret_cast<f16*>(buf)[frag16_elem_offset(R, row, k)] = to_kv(v);
-    else store_operand<kDtBf16>(buf, R, 0, row, k, v);
-}
-
+// Four elements in the format a prompt pass runs in: fp16 plane (f16_plane != 0) or the bf16 hi / lo planes.
 __device__ __forceinline__ void store_operand4_fmt(void* buf, int R, int row, int k, f32x4 v, int f16_plane) {
     if (f16_plane) {
         typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;

@@ -4,10 +4,11 @@
 // are organised around keeping 16-byte-per-lane weight loads in flight; MFMA does the arithmetic because the
 // vector ALUs could not keep up with 16..32 rows at 8 TB/s.
 //
-// bf16 kernel: a wavefront streams a k-slice of one tile of 16 output features (contiguous in the packed weight
+// bf16 kernels: a wavefront streams a k-slice of one or several tiles of 16 output features (contiguous in the packed weight
 // order) with a register double buffer of P fragments; the activation fragments (hi and lo planes) come from L2/L1
-// in the same order. Partial tiles are reduced in a fixed order (deterministic, independent of the number of rows)
-// through LDS and, when K is also split across workgroups, through a scratch buffer; then the epilogue runs.
+// in the same order. Partial tiles are added in a fixed order through LDS (the same call twice gives the same bits; how K
+// is cut follows the numbers of rows and tiles), then the epilogue runs. Slices of different workgroups (kEpiPartial) are
+// left to the next kernel.
 //
 // Epilogues (they produce what the NEXT kernel consumes, so that no separate norm / rotary / activation kernels
 // exist):
@@ -779,8 +780,8 @@ __global__ __launch_bounds__(KW * 64) void gemm_bf16_resident_kernel(GEMM_LEAD_P
 // requested at once and the chain behind it is kept short. One workgroup per tile of 16 output features, eight
 // wavefronts that split K; a lane loads 16 bytes of W[feature lane%16] and of A[row lane%16] per 16 k (its four k are
 // step*16 + (lane/16)*4 + 0..3 on both sides, so element m of the two loads is one v_mfma_f32_16x16x4_f32, whose order of
-// k inside a step is free), and the four elements go into four accumulators, so that no sum is longer than K/128 + 10
-// additions. The slices are added in wavefront order through LDS; wavefront rg then runs the epilogue of row group rg on
+// k inside a step is free), and the four elements go into four accumulators: each takes K/32 products, K/128 instructions
+// of four, before the four and then the eight slices are added up. The slices are added in wavefront order through LDS; wavefront rg then runs the epilogue of row group rg on
 // a transposed tile (a lane owns four consecutive features of a row: 16-byte loads and stores).
 // Measured at d = 256, 5 rows: 47-85 us per launch with four features after one another per wavefront, a lane's FMAs for
 // 32 rows and 32 x 6 shuffles per feature; 4.1 us (projections onto d), 5.2 (q, k, v) and 6.6 (gate and up) now. Error
