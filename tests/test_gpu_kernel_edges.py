@@ -140,6 +140,41 @@ def test_fp32_attention_depends_on_no_stale_lds(T):
     eng.close()
 
 
+# head_dim not a multiple of 8 (fp32 models; matrices handed over as they are, which is what packing does to them): the attention
+# goes element by element. Fewer and more rotary pairs than a wavefront has lanes, prefixes up to 109 tokens, LDS full of NaN.
+# Bounds as for the projections above.
+@pytest.mark.parametrize("heads,kv,hd", [(8, 8, 6), (16, 8, 10), (8, 8, 130)])
+def test_fp32_attention_with_odd_head_sizes(heads, kv, hd):
+    import paper_2505_24196_amd as clasp
+    from tests.lds_fill import load
+    fill = load()
+    shape = si.ModelShape("edge-f32-odd", 3, 64, heads, kv, hd, 48, 112, "f32")
+    model = si.gen_model(shape, 3, "cpu")
+    om = oc.OracleModel(shape, si.model_to_numpy(model))
+    eng = clasp.Engine(shape, max_seq=128, max_rows=32)
+    eng.set_head(model["embed"], model["lm_head"], model["final_norm"])
+    for l, w in enumerate(model["layers"]):
+        t = {k: v.cuda().contiguous() for k, v in w.items()}
+        t["w_gate_up"] = torch.cat([t.pop("w_gate"), t.pop("w_up")])
+        eng._layers[l] = t
+    eng.create()
+    cache = oc.KVCache(shape, 128)
+    toks, pos = [int(t) for t in si.gen_tokens(5, 109, shape.vocab)], 0
+    for n in (1, 2, 7, 32, 32, 1, 2, 32):
+        fill(0x7fc00000)
+        out = eng.clasp_verify_forward(torch.tensor(toks[pos:pos + n], dtype=torch.int32, device="cuda"), pos, want_hidden=True, want_logits=True)
+        ref = [om.token(t, pos + i, cache, want_states=True) for i, t in enumerate(toks[pos:pos + n])]
+        assert_close(out["hidden"].cpu().numpy(), np.stack([r[0] for r in ref], 1), 2e-5, f"{n} rows at {pos}: hidden")
+        assert_close(out["logits"].cpu().numpy(), np.stack([r[1] for r in ref]), 2e-5, f"{n} rows at {pos}: logits")
+        pos += n
+    X = out["hidden"][:, -1].contiguous()
+    fill(0x7fc00000)
+    gpu = eng.clasp_dp_select(X, pos - 1, 2, want_tables=True)
+    dp = oracle_dp_following(om, X.cpu().numpy().astype(np.float64), pos - 1, cache, 2, gpu["choice"].cpu().numpy())
+    assert_close(gpu["g_final"].cpu().numpy(), dp["g_final"], 2e-5, "g(L, M)")
+    eng.close()
+
+
 # Draws and acceptance: in one launch (a draw up to 4096 entries, one to four a thread; acceptance up to 1024 entries and seven
 # drafts), in two (acceptance up to 4096) and over rows cut into chunks, the last of them of 16 entries, 64 full ones,
 # larger than what stays in registers. The mass sits on at most eight tokens, several of them at chunk edges. A running sum of the
